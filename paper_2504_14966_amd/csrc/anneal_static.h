@@ -691,13 +691,11 @@ namespace sa {
 // T32: every time on the timeline fits 32 bits (the host's check; not with DETAIL): the batch
 // starts come from a 32-bit scan of the batch durations that begins at the batch size (the
 // duration is the same on every lane of a batch) and the latency sum from 16-bit halves.
-template <int LG, bool DETAIL, bool T32 = false>
-__global__ void __launch_bounds__(256) eval_static_kernel(DevModel m, StaticParams sp, QueuePtrs q,
-                                                           const uint16_t *__restrict__ perms, int64_t rows,
-                                                           int64_t *__restrict__ out, int64_t *__restrict__ detail) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const EvalRows span = eval_gate(q, m, rows, out);
-  if (span.end <= span.begin) return;
+template <int LG, bool DETAIL, bool T32>
+__device__ __forceinline__ void eval_static_rows(const DevModel &m, const StaticParams &sp, const QueuePtrs &q,
+                                                 const uint16_t *__restrict__ perms, const EvalRows span,
+                                                 int64_t *__restrict__ out, int64_t *__restrict__ detail,
+                                                 unsigned char *lds) {
   constexpr int Bp = 1 << LG, G = kWave >> LG;
   const int n = m.n, B = m.B;
   const int M = (n + B - 1) / B, R = (M + G - 1) / G;
@@ -832,6 +830,22 @@ __global__ void __launch_bounds__(256) eval_static_kernel(DevModel m, StaticPara
     }
     wave_sync_lds();
   }
+}
+
+template <int LG, bool DETAIL>
+__global__ void __launch_bounds__(256) eval_static_kernel(DevModel m, StaticParams sp, QueuePtrs q,
+                                                           const uint16_t *__restrict__ perms, int64_t rows,
+                                                           int64_t *__restrict__ out, int64_t *__restrict__ detail) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const EvalRows span = eval_gate(q, m, rows, out);
+  if (span.end <= span.begin) return;
+  if constexpr (!DETAIL) {
+    if (m.flags & kFlagTime32) {
+      eval_static_rows<LG, false, true>(m, sp, q, perms, span, out, nullptr, lds);
+      return;
+    }
+  }
+  eval_static_rows<LG, DETAIL, false>(m, sp, q, perms, span, out, detail, lds);
 }
 
 }  // namespace sa

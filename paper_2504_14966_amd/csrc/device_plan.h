@@ -236,24 +236,23 @@ __device__ __forceinline__ bool gate_status(const unsigned char *ws, const Gate 
   return true;
 }
 
-// Every row of an evaluation call whose queue failed the checks reads (-2, code).
-__device__ __forceinline__ void error_rows(int64_t rows, int32_t status, int64_t *out) {
+// Every row of an evaluation call reads (a, b): (-2, code) when its queue failed the checks.
+__device__ __forceinline__ void fill_rows(int64_t rows, int64_t a, int64_t b, int64_t *out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < rows; r += stride) {
-    out[2 * r] = -2;
-    out[2 * r + 1] = status;
+    out[2 * r] = a;
+    out[2 * r + 1] = b;
   }
 }
 
 // Evaluation calls have no workspace. The first candidate launched forms the verdict in
 // every workgroup: on a failed check it writes the error rows; when another candidate is
-// selected, its workgroup 0 leaves the verdict in row 0 of the output as a marker
-// (kEvalMarker - selected, flags) and no row is replayed. A later candidate reads the marker
-// and, when it is the one selected, replays rows 1 .. rows - 1; the fix-up launch after
-// every candidate (self == kEvalFixup) finds the marker still there and replays row 0. Row
-// 0 is written by no candidate that reads it, so no workgroup can see it overwritten.
+// selected, it replays no row and leaves the verdict in every row of the output as a marker
+// (kEvalMarker - selected, flags). A workgroup of a later candidate reads the marker of the
+// first row it replays itself, which no other workgroup writes, so none can see it
+// overwritten; the barrier between this read and its own waves' first results is the one
+// after the request records are staged.
 constexpr int64_t kEvalMarker = -16;
-constexpr int32_t kEvalFixup = -2;
 
 struct EvalRows {
   int64_t begin, end;  // rows this launch replays (none when end <= begin)
@@ -265,22 +264,18 @@ template <class PlanFn>
 __device__ __forceinline__ EvalRows eval_rows_of(PlanFn plan, const Gate &g, int64_t rows, int64_t *out,
                                                  uint32_t &flags) {
   if (g.self != 0) {
-    const int64_t mark = out[0];
-    const bool mine = g.self == kEvalFixup ? mark <= kEvalMarker : mark == kEvalMarker - g.self;
-    if (!mine) return EvalRows{0, 0};
-    flags |= (uint32_t)out[1] & g.allow;
-    return g.self == kEvalFixup ? EvalRows{0, 1} : EvalRows{1, rows};
+    const int64_t *own = out + 2 * (int64_t)blockIdx.x * (blockDim.x >> 6);
+    if (own[0] != kEvalMarker - g.self) return EvalRows{0, 0};
+    flags |= (uint32_t)own[1] & g.allow;
+    return EvalRows{0, rows};
   }
   const Plan p = plan();
   if (p.status != 0) {
-    error_rows(rows, p.status, out);
+    fill_rows(rows, -2, p.status, out);
     return EvalRows{0, 0};
   }
   if (p.selected != 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      out[0] = kEvalMarker - p.selected;
-      out[1] = (int64_t)p.flags;
-    }
+    fill_rows(rows, kEvalMarker - p.selected, (int64_t)p.flags, out);
     return EvalRows{0, 0};
   }
   flags |= p.flags & g.allow;

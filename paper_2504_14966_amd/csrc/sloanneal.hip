@@ -184,6 +184,17 @@ int device_attr(hipDeviceAttribute_t attr, int fallback) {
 int max_lds_per_block() { return device_attr(hipDeviceAttributeMaxSharedMemoryPerBlock, 65536); }
 int cu_count() { return device_attr(hipDeviceAttributeMultiprocessorCount, 256); }
 
+// Workgroups of an evaluation launch. Each forms the verdict and stages the requests first,
+// about 3 us: at 32768 rows of 10 requests, 8192 workgroups took 56 us and 2048 (what the GPU
+// holds at once) 25 us. Beyond that as many as leave every wave four rows, at most 8192: with
+// 2^20 rows of 128 requests, 2048 workgroups end unevenly (eval_static_kernel 678 us against
+// 551 us), and at 131072 rows of 400 requests 2048 take 376 us, 8192 take 332 us.
+int eval_grid(int64_t rows, int waves, size_t lds, int lim, int cus) {
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / waves, (int64_t)lim / (int64_t)(lds + sa::kCheckLdsBytes)));
+  const int64_t most = std::max<int64_t>(per_cu * cus, std::min<int64_t>(8192, rows / (4 * waves)));
+  return (int)std::min<int64_t>((rows + waves - 1) / waves, most);
+}
+
 size_t sized_chain_lds(int n) {
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t ub = ((size_t)n * 4 + 15) & ~size_t(15);
@@ -611,16 +622,14 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
     while ((1 << lg) < model->max_batch) ++lg;
     const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
     const size_t lds = (size_t)(n + 1) * 16 + ((((size_t)n * 2 + 15) & ~size_t(15)) + 64 * 8 + 32 * 4) * 4;
-    const int g4 = (int)std::min<int64_t>((k + 3) / 4, 256 * 32);
-    auto launch = [=](const sa::DevModel &d, bool t32) {
-#define SA_EVAL_CASE(L)                                                                                        \
-  case L:                                                                                                      \
-    if (detail)                                                                                                \
-      sa::eval_static_kernel<L, true><<<g4, 256, lds, stream>>>(d, sp, qp, perms, k, out, detail);             \
-    else if (t32)                                                                                              \
-      sa::eval_static_kernel<L, false, true><<<g4, 256, lds, stream>>>(d, sp, qp, perms, k, out, nullptr);     \
-    else                                                                                                       \
-      sa::eval_static_kernel<L, false><<<g4, 256, lds, stream>>>(d, sp, qp, perms, k, out, nullptr);           \
+    const int g4 = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
+    c.add(kSN, kEvalFlags | kT32, [=](const sa::DevModel &d) {
+#define SA_EVAL_CASE(L)                                                                            \
+  case L:                                                                                          \
+    if (detail)                                                                                    \
+      sa::eval_static_kernel<L, true><<<g4, 256, lds, stream>>>(d, sp, qp, perms, k, out, detail);   \
+    else                                                                                           \
+      sa::eval_static_kernel<L, false><<<g4, 256, lds, stream>>>(d, sp, qp, perms, k, out, nullptr); \
     break;
       switch (lg) {
         SA_EVAL_CASE(0)
@@ -634,9 +643,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
       }
 #undef SA_EVAL_CASE
       return hipGetLastError();
-    };
-    if (!detail) c.add(kSN | kT32, kEvalFlags, [=](const sa::DevModel &d) { return launch(d, true); });
-    c.add(kSN, kEvalFlags, [=](const sa::DevModel &d) { return launch(d, false); });
+    });
   }
   // any widths: one order per wave, up to four waves per workgroup as the LDS allows (with
   // room for list scheduling under continuous admission)
@@ -645,27 +652,20 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
   int waves = sa::kWavesPerBlock;
   while (waves > 1 && eval_lds_bytes(n, ls, waves) > lim) waves >>= 1;
   const size_t lds = eval_lds_bytes(n, ls, waves);
-  const int grid = (int)std::min<int64_t>((k + waves - 1) / waves, 256 * 32);
-  auto generic = [=](const sa::DevModel &d, int g) {
+  const int grid = eval_grid(k, waves, lds, max_lds_per_block(), cu_count());
+  c.add(0u, kEvalFlags, [=](const sa::DevModel &d) {
     const void *fn = detail ? (const void *)&sa::eval_kernel<true> : (const void *)&sa::eval_kernel<false>;
     if (lds > 65536) {
       const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
     if (detail)
-      sa::eval_kernel<true><<<g, waves * 64, lds, stream>>>(d, qp, perms, k, out, detail);
+      sa::eval_kernel<true><<<grid, waves * 64, lds, stream>>>(d, qp, perms, k, out, detail);
     else
-      sa::eval_kernel<false><<<g, waves * 64, lds, stream>>>(d, qp, perms, k, out, nullptr);
+      sa::eval_kernel<false><<<grid, waves * 64, lds, stream>>>(d, qp, perms, k, out, nullptr);
     return hipGetLastError();
-  };
-  c.add(0u, kEvalFlags, [=](const sa::DevModel &d) { return generic(d, grid); });
-  if ((rc = c.run(dm)) || c.gate.count < 2) return rc;
-  // row 0 when a candidate other than the first replayed the rest (its verdict marker sits
-  // there until now)
-  sa::DevModel fix = c.checker(dm, kEvalFlags);
-  fix.gate.self = sa::kEvalFixup;
-  const hipError_t e = generic(fix, 1);
-  return e == hipSuccess ? SCHED_OK : hip_fail(e);
+  });
+  return c.run(dm);
 }
 
 size_t sched_ws_bytes(int32_t n, int32_t chains) {
@@ -769,9 +769,9 @@ int sched_eval_batches(const sched_queue_t *queue, const sched_model_t *model, c
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (pb + fb + 64 * 16 + 32 * 4);
-  const int grid = (int)std::min<int64_t>((k + 3) / 4, 256 * 32);
+  const int grid = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
   Candidates<sa::DevModel> c;
-  // one kernel: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
+  // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
   // where they hold
   c.add(0u, sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {
     if (detail)
@@ -881,7 +881,7 @@ int sched_eval_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, con
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (pb + fb + 32 * 4);
-  const int grid = (int)std::min<int64_t>((k + 3) / 4, 256 * 32);
+  const int grid = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
   Candidates<sa::DevFit> c;
   c.add(0u, sa::kFlagFitWindows, [=](const sa::DevFit &d) {
     if (detail)
