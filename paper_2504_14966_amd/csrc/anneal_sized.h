@@ -316,7 +316,50 @@ __device__ __forceinline__ Score replay_batches(const DevModel &m, const uint4 *
   return replay_batches_one<DETAIL>(m, req, perm, flags, stage, detail);
 }
 
-// K rows of (order, layout): one wave per row, rows validated first ((-1, -1) otherwise).
+// LDS one wave needs to validate and replay one (order, layout) row: order, flags, the
+// replay's staging and the validity bitmap.
+__host__ __device__ __forceinline__ size_t sized_row_bytes(int n) {
+  return (((size_t)n * 2 + 15) & ~size_t(15)) + (((size_t)n + 15) & ~size_t(15)) + 64 * 16 + 32 * 4;
+}
+
+// One (order, layout) row by one wave: validated ((-1, -1) otherwise), then replayed.
+template <bool DETAIL>
+__device__ __forceinline__ void eval_sized_row(const DevModel &m, const uint4 *__restrict__ req,
+                                               const uint16_t *__restrict__ src, const uint8_t *__restrict__ fsrc,
+                                               unsigned char *wb, int64_t *__restrict__ out, int64_t *detail) {
+  const int n = m.n, lane = lane_id();
+  const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
+  uint16_t *perm = reinterpret_cast<uint16_t *>(wb);
+  uint8_t *flags = wb + pb;
+  uint4 *stage = reinterpret_cast<uint4 *>(wb + pb + fb);
+  uint32_t *bitmap = reinterpret_cast<uint32_t *>(wb + pb + fb + 64 * 16);
+  if (lane < 32) bitmap[lane] = 0u;
+  wave_sync_lds();
+  bool bad = false;
+  for (int p = lane; p < n; p += kWave) {
+    const uint32_t v = src[p];
+    perm[p] = (uint16_t)v;
+    flags[p] = fsrc[p];
+    if (v >= (uint32_t)n) {
+      bad = true;
+    } else {
+      const uint32_t bit = 1u << (v & 31u);
+      const uint32_t old = atomicOr(&bitmap[v >> 5], bit);
+      if (old & bit) bad = true;
+    }
+  }
+  wave_sync_lds();
+  Score s{-1, ~0ull};
+  if (__ballot(bad) == 0ull && layout_ok(flags, n, m.B, lane))
+    s = replay_batches<DETAIL>(m, req, perm, flags, stage, detail);
+  if (lane == 0) {
+    out[0] = s.n;
+    out[1] = (int64_t)s.t;
+  }
+  wave_sync_lds();
+}
+
+// K rows of (order, layout): one wave per row.
 template <bool DETAIL>
 __global__ void __launch_bounds__(256) eval_sized_kernel(DevModel m, QueuePtrs q, const uint16_t *__restrict__ perms,
                                                           const uint8_t *__restrict__ starts, int64_t rows,
@@ -326,56 +369,18 @@ __global__ void __launch_bounds__(256) eval_sized_kernel(DevModel m, QueuePtrs q
   if (span.end <= span.begin) return;
   const int n = m.n;
   uint4 *req = reinterpret_cast<uint4 *>(lds);
-  const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
-  const size_t per_wave = pb + fb + 64 * 16 + 32 * 4;
   const int wave = uniform((int)(threadIdx.x >> 6));
-  unsigned char *wb = lds + (((size_t)n * 16 + 15) & ~size_t(15)) + (size_t)wave * per_wave;
-  uint16_t *perm = reinterpret_cast<uint16_t *>(wb);
-  uint8_t *flags = wb + pb;
-  uint4 *stage = reinterpret_cast<uint4 *>(wb + pb + fb);
-  uint32_t *bitmap = reinterpret_cast<uint32_t *>(wb + pb + fb + 64 * 16);
+  unsigned char *wb = lds + (((size_t)n * 16 + 15) & ~size_t(15)) + (size_t)wave * sized_row_bytes(n);
   for (int r = threadIdx.x; r < n; r += blockDim.x) {
     const uint32_t lin = q.in_len[r], lout = q.out_len[r];
     req[r] = make_uint4(lin | (lout << 16), q.thr[r], (uint32_t)q.kind[r], 0u);
   }
   __syncthreads();
-  const int lane = lane_id();
   const int waves = blockDim.x >> 6;
   for (int64_t row = span.begin + (int64_t)blockIdx.x * waves + wave; row < span.end;
-       row += (int64_t)gridDim.x * waves) {
-    const uint16_t *src = perms + row * n;
-    const uint8_t *fsrc = starts + row * n;
-    if (lane < 32) bitmap[lane] = 0u;
-    wave_sync_lds();
-    bool bad = false;
-    for (int p = lane; p < n; p += kWave) {
-      const uint32_t v = src[p];
-      perm[p] = (uint16_t)v;
-      flags[p] = fsrc[p];
-      if (v >= (uint32_t)n) {
-        bad = true;
-      } else {
-        const uint32_t bit = 1u << (v & 31u);
-        const uint32_t old = atomicOr(&bitmap[v >> 5], bit);
-        if (old & bit) bad = true;
-      }
-    }
-    wave_sync_lds();
-    const bool ok = __ballot(bad) == 0ull && layout_ok(flags, n, m.B, lane);
-    if (!ok) {
-      if (lane == 0) {
-        out[2 * row] = -1;
-        out[2 * row + 1] = -1;
-      }
-      continue;
-    }
-    const Score s = replay_batches<DETAIL>(m, req, perm, flags, stage, DETAIL ? detail + row * n * 2 : nullptr);
-    if (lane == 0) {
-      out[2 * row] = s.n;
-      out[2 * row + 1] = (int64_t)s.t;
-    }
-    wave_sync_lds();
-  }
+       row += (int64_t)gridDim.x * waves)
+    eval_sized_row<DETAIL>(m, req, perms + row * n, starts + row * n, wb, out + 2 * row,
+                           DETAIL ? detail + row * n * 2 : nullptr);
 }
 
 // Proposal draws of the joint search, 64 iterations per Philox pass (lane l: iteration

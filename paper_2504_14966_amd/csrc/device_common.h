@@ -79,6 +79,8 @@ constexpr int kFlagFitWindows = 64;    // fitted model: the timeline (and every 
 constexpr int kFlagFitMember32 = 128;  // fitted model: every member's time, in any batch, below 2^32 - 1
 constexpr int kFlagInst64 = 256;       // several instances: each holds at most 64 requests
 constexpr int kFlagInst192 = 512;      // several instances: each holds at most 192 requests
+// evaluation calls only (no workspace header ever holds it)
+constexpr int kFlagEvalLaneSums = 1024;  // one order per lane, static: 24-bit factors of a batch's running sums
 constexpr uint64_t kWsMagic = 0x534c4f414e4e3031ull;  // "SLOANN01"
 
 __host__ __device__ __forceinline__ size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

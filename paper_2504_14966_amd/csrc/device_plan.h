@@ -207,11 +207,28 @@ __device__ QueueStats block_queue_stats(const QueuePtrs &q, int n, int B, int ma
   return s;
 }
 
-// The plan of an integer-model call, formed by the whole workgroup.
+// Widths of the kernels that score one order per lane, on top of plan_decide's flags (which
+// bound every term below). Static: a batch's sum of d1 + d2 l over its members, and
+// d2 L (L + 1) / 2, are factors of 24 bits.
+__host__ __device__ inline uint32_t eval_lane_flags(const QueueStats &s, int n, int B, uint64_t d1, uint64_t d2,
+                                                    uint32_t flags) {
+  constexpr uint64_t two24 = 1ull << 24;
+  const uint64_t b = (uint64_t)(n < B ? n : B), L = s.Lmax, tri = L * (L + 1) / 2;
+  uint32_t f = 0u;
+  if ((flags & kFlagStaticNarrow) && b * (d1 + d2 * s.lmax) < two24 && d2 * tri < two24) f |= kFlagEvalLaneSums;
+  return f;
+}
+
+// The plan of an integer-model call, formed by the whole workgroup (LANES: an evaluation
+// call's, with the widths of the one-order-per-lane kernels).
+template <bool LANES = false>
 __device__ __forceinline__ Plan plan_in_block(const QueuePtrs &q, const DevModel &m) {
   const QueueStats s = block_queue_stats(q, m.n, m.B, m.max_kind, nullptr);
   Plan p = plan_decide(s, m.n, m.B, m.ratio, m.t_ref, m.p0, m.p1, m.d0, m.d1, m.d2, nullptr, m.gate);
-  if (p.status == 0) p.selected = plan_select(m.gate, p.flags);
+  if (p.status == 0) {
+    if (LANES) p.flags |= eval_lane_flags(s, m.n, m.B, m.d1, m.d2, p.flags);
+    p.selected = plan_select(m.gate, p.flags);
+  }
   return p;
 }
 
@@ -284,7 +301,7 @@ __device__ __forceinline__ EvalRows eval_rows_of(PlanFn plan, const Gate &g, int
 
 __device__ __forceinline__ EvalRows eval_gate(const QueuePtrs &q, DevModel &m, int64_t rows, int64_t *out) {
   uint32_t f = 0u;
-  const EvalRows r = eval_rows_of([&]() { return plan_in_block(q, m); }, m.gate, rows, out, f);
+  const EvalRows r = eval_rows_of([&]() { return plan_in_block<true>(q, m); }, m.gate, rows, out, f);
   m.flags |= (int32_t)f;
   return r;
 }

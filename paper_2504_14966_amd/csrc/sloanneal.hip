@@ -18,6 +18,7 @@
 #include "anneal_static.h"
 #include "anneal_wave.h"
 #include "anneal_sized.h"
+#include "eval_lanes.h"
 #include "anneal_wave_rows.h"
 #include "anneal_cont_spec.h"
 #include "multi.h"
@@ -87,6 +88,12 @@ constexpr uint32_t kAnnealFlags = sa::kFlagNarrowPrefill | sa::kFlagListSched | 
 constexpr uint32_t kEvalFlags = sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime;
 constexpr uint32_t kMultiFlags = kEvalFlags;
 constexpr uint32_t kSN = sa::kFlagStaticNarrow, kT32 = sa::kFlagTime32;
+// Rows from which evaluation runs with one order per lane: a tile of 64 orders then takes a
+// wave about as long as the one-order-per-wave kernels take for all rows, and every SIMD has
+// one. Measured crossings (us, lanes against waves): static, 128 requests, batches of 16: 33
+// against 34 at 32768 rows, 35 against 51 at 65536, but batches of 4 only 37 against 41 at
+// 65536 (38 against 32 at 32768); layouts, the same queue: 39 against 52 at 16384.
+int64_t eval_lane_rows(int n, int B, bool layout) { return layout ? 16384 : (n <= 64 || B >= 16 ? 32768 : 65536); }
 
 // The kernels one call may run, in order of preference, each with the width flags it needs
 // and the ones it may use. All of them are enqueued; on the device each reads the verdict of
@@ -572,6 +579,33 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
   });
 }
 
+// Static evaluation with one order per lane, for enough rows to give every SIMD a wave and
+// short enough queues for the LDS to hold four waves per CU.
+template <bool LAYOUT>
+void add_eval_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
+                    const uint16_t *perms, const uint8_t *starts, int64_t k, int64_t *out, hipStream_t stream) {
+  const int cus = std::max(1, cu_count()), lim = max_lds_per_block() - (int)sa::kCheckLdsBytes;
+  if (n < 2 || k < eval_lane_rows(n, model->max_batch, LAYOUT)) return;
+  // the tile's ids and flags are read 16 bytes at a time (a tile of 64 rows keeps the alignment)
+  if ((reinterpret_cast<uintptr_t>(perms) | reinterpret_cast<uintptr_t>(starts)) & 15u) return;
+  const int M = (n + model->max_batch - 1) / model->max_batch;
+  const int mcap = LAYOUT ? std::min(n, 3 * M + 4) : M;
+  const size_t shared = sa::lane_shared_bytes(n, LAYOUT), per = sa::lane_wave_bytes(n, mcap, LAYOUT);
+  if (mcap > 254 || shared + 4 * per > (size_t)lim) return;
+  const size_t lds = shared + 4 * per;
+  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / lds)));
+  const int grid = (int)std::min<int64_t>((k + 255) / 256, (int64_t)cus * per_cu);
+  c.add(kSN | kT32 | sa::kFlagEvalLaneSums, kEvalFlags | sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {
+    const void *fn = (const void *)&sa::eval_lanes_kernel<LAYOUT>;
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    sa::eval_lanes_kernel<LAYOUT><<<grid, 256, lds, stream>>>(d, qp, perms, starts, k, out, mcap);
+    return hipGetLastError();
+  });
+}
+
 // Fixed device scratch of sched_anneal_noalloc: the annealing workspace for callers that
 // cannot allocate. Each GPU the library runs on holds its own copy until the process ends.
 // Host code never passes the array's name to a kernel (on the host it is only a stand-in for
@@ -623,6 +657,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
     const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
     const size_t lds = (size_t)(n + 1) * 16 + ((((size_t)n * 2 + 15) & ~size_t(15)) + 64 * 8 + 32 * 4) * 4;
     const int g4 = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
+    if (!detail) add_eval_lanes<false>(c, model, n, qp, perms, nullptr, k, out, stream);
     c.add(kSN, kEvalFlags | kT32, [=](const sa::DevModel &d) {
 #define SA_EVAL_CASE(L)                                                                            \
   case L:                                                                                          \
@@ -767,10 +802,10 @@ int sched_eval_batches(const sched_queue_t *queue, const sched_model_t *model, c
   if (k == 0) return SCHED_OK;
   const int n = queue->n;
   const sa::QueuePtrs qp = dev_queue(queue);
-  const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
-  const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (pb + fb + 64 * 16 + 32 * 4);
+  const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * sa::sized_row_bytes(n);
   const int grid = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
   Candidates<sa::DevModel> c;
+  if (!detail) add_eval_lanes<true>(c, model, n, qp, perms, starts, k, out, stream);
   // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
   // where they hold
   c.add(0u, sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {

@@ -1,7 +1,8 @@
 """Evaluation paths that depend on the number of rows, against the oracle (bit-exact).
 
 Candidate launches: a call whose first candidate is not the one selected, with more rows than
-one pass of the grid.
+one pass of the grid. One order per lane: row counts that reach those kernels, every row against
+the one-order-per-wave kernels (reached by calls of few rows) and a sample against the oracle.
 """
 import os
 import sys
@@ -53,3 +54,113 @@ def test_later_candidate_with_many_rows(sl, orc, d2):
     assert (got[bad] == -1).all()
     some = np.concatenate([np.arange(0, 50_000, 7), np.arange(49_000, 50_000)])
     assert np.array_equal(got[some], oracle_rows(q, m, p[some]))
+
+
+def _layouts(rng, k, n, B):
+    """k x n start flags, batch sizes uniform in 1..B."""
+    out = np.zeros((k, n), np.uint8)
+    at = np.zeros(k, np.int64)
+    rows = np.arange(k)
+    while len(rows):
+        out[rows, at[rows]] = 1
+        at[rows] += rng.integers(1, B + 1, len(rows))
+        rows = rows[at[rows] < n]
+    return out
+
+
+# (n, B): one to many batches per lane, rows that straddle the 16-byte chunks of ids and flags,
+# 32-position words with a remainder, the largest that fits, and batches of the whole queue
+LANES = [(2, 1), (7, 3), (10, 4), (16, 16), (33, 8), (64, 64), (100, 24), (128, 16), (200, 64)]
+
+
+@pytest.mark.parametrize("n,B", LANES)
+@pytest.mark.parametrize("rows", [65536, 65536 + 77])
+def test_static_lanes(sl, orc, n, B, rows):
+    rng = np.random.default_rng(1000 * n + B + rows)
+    q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
+    m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2)
+    p = _orders(rng, rows, n)
+    bad = [0, 63, 64, 65, 127, rows // 2, rows - 64, rows - 1]
+    _spoil(p, bad, rng)
+    dq, dp = sl.DeviceQueue.from_queue(q), sl.perms_to_device(p)
+    got = sl.sched_eval(dq, m, dp).cpu().numpy()
+    assert (got[bad] == -1).all()
+    # every row against the one-order-per-wave kernel (a call of few rows), a sample against the oracle
+    want = np.concatenate([sl.sched_eval(dq, m, c.contiguous()).cpu().numpy() for c in dp.split(8192)])
+    assert np.array_equal(got, want)
+    some = rng.integers(0, rows, 256)
+    assert np.array_equal(got[some], orc.eval_rows(q, m, p[some]))
+
+
+@pytest.mark.parametrize("n,B", LANES + [(40, 2), (300, 64)])
+@pytest.mark.parametrize("rows", [16384, 16384 + 77])
+def test_layout_lanes(sl, orc, n, B, rows):
+    # (40, 2): some valid layouts have more batches than a lane's entries hold
+    rng = np.random.default_rng(1000 * n + B + rows + 1)
+    q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
+    m = Model(B, 2, p0=2000, p1=40, d0=8000, d1=300, d2=2)
+    p, s = _orders(rng, rows, n), _layouts(rng, rows, n, B)
+    s[rng.integers(0, rows, 40)] = 1  # every request alone
+    full = rng.integers(0, rows, 40)
+    s[full] = (np.arange(n) % B == 0)
+    bad = [0, 63, 64, 65, rows - 64, rows - 1]
+    _spoil(p, bad, rng)
+    # layouts that are not valid: no start at 0, a flag of 2 or 255, a batch one too long
+    for i, r in enumerate((5, 66, 130, 4000, rows - 5)):
+        if i == 0:
+            s[r, 0] = 0
+        elif i < 3:
+            s[r, rng.integers(0, n)] = (2, 255)[i - 1]
+        elif n > B:
+            s[r] = (np.arange(n) % B == 0)
+            at = B * rng.integers(1, (n - 1) // B + 1)
+            s[r, at] = 0
+        else:
+            s[r, 0] = 3
+        bad.append(r)
+    dq, dp, ds = sl.DeviceQueue.from_queue(q), sl.perms_to_device(p), sl.starts_to_device(s)
+    got = sl.sched_eval_batches(dq, m, dp, ds).cpu().numpy()
+    assert (got[bad] == -1).all()
+    want = np.concatenate([sl.sched_eval_batches(dq, m, a.contiguous(), b.contiguous()).cpu().numpy()
+                           for a, b in zip(dp.split(8192), ds.split(8192))])
+    assert np.array_equal(got, want)
+    some = rng.integers(0, rows, 256)
+    assert np.array_equal(got[some], orc.eval_rows_batches(q, m, p[some], s[some]))
+
+
+@pytest.mark.parametrize("field,value", [("d1", (1 << 24) // 16 - 1), ("d1", (1 << 24) // 16), ("out", 5792),
+                                         ("out", 5793)])
+def test_static_lanes_widths(sl, orc, field, value):
+    # both sides of the 24-bit factors: a full batch's sum of d1, and d2 L (L + 1) / 2 with d2 = 1
+    rng = np.random.default_rng(value)
+    n, B, rows = 24, 16, 32768
+    q = random_queue(rng, n, max_in=60, max_out=15, thr_hi=1_000_000_000)
+    m = Model(B, 0, p0=10, p1=1, d0=10, d1=300, d2=0)
+    if field == "d1":
+        m.d1 = value
+        q.out_len[:] = rng.integers(1, 9, n)
+    else:
+        m.d2 = 1
+        q.out_len[3] = value
+    p = _orders(rng, rows, n)
+    got = sl.sched_eval(sl.DeviceQueue.from_queue(q), m, sl.perms_to_device(p)).cpu().numpy()
+    some = np.arange(0, rows, 11)
+    assert np.array_equal(got[some], orc.eval_rows(q, m, p[some]))
+
+
+def test_lanes_unaligned_rows(sl, orc):
+    # orders and flags that do not begin at a 16-byte boundary go to the one-order-per-wave kernels
+    import torch
+    rng = np.random.default_rng(3)
+    n, B, rows = 10, 4, 40_000
+    q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
+    m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2)
+    p, s = _orders(rng, rows + 1, n), _layouts(rng, rows + 1, n, B)
+    dq = sl.DeviceQueue.from_queue(q)
+    dp = torch.from_numpy(p.view(np.int16)).cuda()[1:]
+    ds = torch.from_numpy(s).cuda()[1:]
+    assert dp.data_ptr() % 16 and ds.data_ptr() % 16
+    some = np.arange(0, rows, 17)
+    assert np.array_equal(sl.sched_eval(dq, m, dp).cpu().numpy()[some], orc.eval_rows(q, m, p[1:][some]))
+    assert np.array_equal(sl.sched_eval_batches(dq, m, dp, ds).cpu().numpy()[some],
+                          orc.eval_rows_batches(q, m, p[1:][some], s[1:][some]))

@@ -129,3 +129,35 @@ def test_limit_rows_decide_like_the_slo_test():
     want = np.where(kind == 0, ttft <= thr, np.where(kind == 2, e2e <= thr, (e2e - ttft) <= thr * lout))
     assert np.array_equal(got, want)
     assert want.any() and (~want).any()
+
+
+def test_static_offsets_by_descending_output_length(orc):
+    """The one-order-per-lane evaluation takes a batch's members in descending output length and
+    forms F - P - L d0 of each as U + L E + cnt q from three running sums (h of itself and the
+    shorter ones, d1 + d2 l and the count of the ones before it); with q = d2 L (L + 1) / 2 and
+    h = L (d1 + d2 l) + q. Ties in any order. Checked on whole orders against the oracle."""
+    from paper_2504_14966_amd.workloads import Model, random_queue
+    rng = np.random.default_rng(11)
+    for _ in range(60):
+        n, B = int(rng.integers(1, 40)), int(rng.integers(1, 20))
+        q = random_queue(rng, n, max_in=500, max_out=int(rng.integers(1, 60)))
+        m = Model(B, 0, *(int(x) for x in rng.integers(0, [50, 9, 900, 60, 4])))
+        perm = rng.permutation(n)
+        start, met, total = 0, 0, 0
+        for k in range(0, n, B):
+            ids = perm[k:k + B]
+            l, L = (a[ids].astype(np.int64) for a in (q.in_len, q.out_len))
+            qq = m.d2 * L * (L + 1) // 2
+            h = L * (m.d1 + m.d2 * l) + qq
+            P = int((m.p0 + m.p1 * l).sum())
+            U, E, cnt, F = int(h.sum()), 0, 0, np.zeros(len(ids), np.int64)
+            for i in sorted(range(len(ids)), key=lambda i: (-L[i], rng.random())):
+                F[i] = P + L[i] * m.d0 + U + L[i] * E + cnt * qq[i]
+                U, E, cnt = U - int(h[i]), E + int(m.d1 + m.d2 * l[i]), cnt + 1
+            assert F.max() == P + L.max() * m.d0 + h.sum()
+            for i, r in enumerate(ids):
+                thr, e2e, ttft = int(q.thr_us[r]), start + int(F[i]), start + P
+                met += (ttft <= thr, e2e - ttft <= thr * int(L[i]), e2e <= thr)[q.kind[r]]
+                total += e2e
+            start += int(F.max())
+        assert list(orc.replay(q, m, perm.astype(np.uint16))[:2]) == [met, total]
