@@ -209,13 +209,22 @@ __device__ QueueStats block_queue_stats(const QueuePtrs &q, int n, int B, int ma
 
 // Widths of the kernels that score one order per lane, on top of plan_decide's flags (which
 // bound every term below). Static: a batch's sum of d1 + d2 l over its members, and
-// d2 L (L + 1) / 2, are factors of 24 bits.
-__host__ __device__ inline uint32_t eval_lane_flags(const QueueStats &s, int n, int B, uint64_t d1, uint64_t d2,
-                                                    uint32_t flags) {
+// d2 L (L + 1) / 2, are factors of 24 bits. Continuous: so are a decode step, the running
+// context sum, d2 b and s (s + 1) / 2 for a gap s between finishes (at most the longest
+// output); a prefill leaves its top bit free and every time is below 2^32 - 2.
+__host__ __device__ inline uint32_t eval_lane_flags(const QueueStats &s, int n_, int B, uint64_t p0, uint64_t p1,
+                                                    uint64_t d0, uint64_t d1, uint64_t d2, uint32_t flags) {
   constexpr uint64_t two24 = 1ull << 24;
-  const uint64_t b = (uint64_t)(n < B ? n : B), L = s.Lmax, tri = L * (L + 1) / 2;
+  constexpr uint32_t cont = kFlagNarrowPrefill | kFlagListSched | kFlagNarrowTime;
+  const uint64_t n = (uint64_t)n_, b = (uint64_t)(n_ < B ? n_ : B), L = s.Lmax, tri = L * (L + 1) / 2;
   uint32_t f = 0u;
   if ((flags & kFlagStaticNarrow) && b * (d1 + d2 * s.lmax) < two24 && d2 * tri < two24) f |= kFlagEvalLaneSums;
+  if ((flags & cont) == cont) {
+    const uint64_t ctx = b * (s.lmax + L), tl = n * p0 + p1 * s.slin + (d0 + d1) * s.sL + d2 * s.sctx;
+    if (d0 + d1 * b + d2 * ctx < two24 && ctx < two24 && d2 * b < two24 && tri < two24 &&
+        p0 + p1 * s.lmax < (1ull << 31) && tl < (1ull << 32) - 2)
+      f |= kFlagEvalLaneCont;
+  }
   return f;
 }
 
@@ -226,7 +235,7 @@ __device__ __forceinline__ Plan plan_in_block(const QueuePtrs &q, const DevModel
   const QueueStats s = block_queue_stats(q, m.n, m.B, m.max_kind, nullptr);
   Plan p = plan_decide(s, m.n, m.B, m.ratio, m.t_ref, m.p0, m.p1, m.d0, m.d1, m.d2, nullptr, m.gate);
   if (p.status == 0) {
-    if (LANES) p.flags |= eval_lane_flags(s, m.n, m.B, m.d1, m.d2, p.flags);
+    if (LANES) p.flags |= eval_lane_flags(s, m.n, m.B, m.p0, m.p1, m.d0, m.d1, m.d2, p.flags);
     p.selected = plan_select(m.gate, p.flags);
   }
   return p;

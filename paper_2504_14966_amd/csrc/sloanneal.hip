@@ -19,6 +19,7 @@
 #include "anneal_wave.h"
 #include "anneal_sized.h"
 #include "eval_lanes.h"
+#include "eval_cont_lanes.h"
 #include "anneal_wave_rows.h"
 #include "anneal_cont_spec.h"
 #include "multi.h"
@@ -92,8 +93,12 @@ constexpr uint32_t kSN = sa::kFlagStaticNarrow, kT32 = sa::kFlagTime32;
 // wave about as long as the one-order-per-wave kernels take for all rows, and every SIMD has
 // one. Measured crossings (us, lanes against waves): static, 128 requests, batches of 16: 33
 // against 34 at 32768 rows, 35 against 51 at 65536, but batches of 4 only 37 against 41 at
-// 65536 (38 against 32 at 32768); layouts, the same queue: 39 against 52 at 16384.
+// 65536 (38 against 32 at 32768); layouts, the same queue: 39 against 52 at 16384; continuous,
+// 32 running: 58 against 43 at 16384 rows of 128 requests and 58 against 82 at 32768, while
+// with long queues the scans' LDS leaves the other kernel few waves (1024 requests: 1.8 times
+// its rate at 8192 rows) and short ones are over in a few events.
 int64_t eval_lane_rows(int n, int B, bool layout) { return layout ? 16384 : (n <= 64 || B >= 16 ? 32768 : 65536); }
+int64_t eval_cont_lane_rows(int n) { return n >= 768 ? 8192 : (n >= 320 || n <= 24 ? 16384 : 32768); }
 
 // The kernels one call may run, in order of preference, each with the width flags it needs
 // and the ones it may use. All of them are enqueued; on the device each reads the verdict of
@@ -606,6 +611,41 @@ void add_eval_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int
   });
 }
 
+// Continuous evaluation with one order per lane (the list holds the running requests in 8, 16,
+// 32 or 64 registers), for enough rows to give every SIMD a wave.
+void add_eval_cont_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
+                         const uint16_t *perms, int64_t k, int64_t *out, hipStream_t stream) {
+  const int cus = std::max(1, cu_count()), lim = max_lds_per_block() - (int)sa::kCheckLdsBytes;
+  if (k < eval_cont_lane_rows(n)) return;
+  const int n0 = std::min(model->max_batch, n), cap = n0 <= 8 ? 8 : (n0 <= 16 ? 16 : (n0 <= 32 ? 32 : 64));
+  const size_t shared = (size_t)n * 16, per = sa::cont_lane_wave_bytes(n, cap);
+  int waves = 4;
+  while (waves > 1 && shared + waves * per > (size_t)lim) --waves;
+  const size_t lds = shared + waves * per;
+  if (lds > (size_t)lim) return;
+  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / lds)));
+  const int64_t tiles = (k + 63) / 64;
+  const int grid = (int)std::min<int64_t>((tiles + waves - 1) / waves, (int64_t)cus * per_cu);
+  c.add(sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime | sa::kFlagEvalLaneCont, kEvalFlags,
+        [=](const sa::DevModel &d) {
+          auto go = [&](auto kernel) {
+            if (lds > 65536) {
+              const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+              if (e != hipSuccess) return e;
+            }
+            kernel<<<grid, waves * 64, lds, stream>>>(d, qp, perms, k, out);
+            return hipGetLastError();
+          };
+          switch (cap) {
+            case 8: return go(&sa::eval_cont_lanes_kernel<8>);
+            case 16: return go(&sa::eval_cont_lanes_kernel<16>);
+            case 32: return go(&sa::eval_cont_lanes_kernel<32>);
+            default: return go(&sa::eval_cont_lanes_kernel<64>);
+          }
+        });
+}
+
 // Fixed device scratch of sched_anneal_noalloc: the annealing workspace for callers that
 // cannot allocate. Each GPU the library runs on holds its own copy until the process ends.
 // Host code never passes the array's name to a kernel (on the host it is only a stand-in for
@@ -683,6 +723,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
   // any widths: one order per wave, up to four waves per workgroup as the LDS allows (with
   // room for list scheduling under continuous admission)
   const bool ls = model->policy == SCHED_CONTINUOUS;
+  if (ls && !detail) add_eval_cont_lanes(c, model, n, qp, perms, k, out, stream);
   const size_t lim = (size_t)max_lds_per_block() - sa::kCheckLdsBytes;  // the checks' own LDS on top
   int waves = sa::kWavesPerBlock;
   while (waves > 1 && eval_lds_bytes(n, ls, waves) > lim) waves >>= 1;

@@ -164,3 +164,52 @@ def test_lanes_unaligned_rows(sl, orc):
     assert np.array_equal(sl.sched_eval(dq, m, dp).cpu().numpy()[some], orc.eval_rows(q, m, p[1:][some]))
     assert np.array_equal(sl.sched_eval_batches(dq, m, dp, ds).cpu().numpy()[some],
                           orc.eval_rows_batches(q, m, p[1:][some], s[1:][some]))
+
+
+# (n, B): no admission, one, a ragged last part of the staged ids, one running request, every
+# capacity of the list (8, 16, 32, 64 registers) full and not
+CONT = [(2, 1), (9, 8), (10, 4), (20, 16), (24, 64), (50, 17), (64, 32), (97, 33), (130, 64), (400, 8)]
+
+
+@pytest.mark.parametrize("n,B", CONT)
+@pytest.mark.parametrize("ties", [False, True])
+def test_continuous_lanes(sl, orc, n, B, ties):
+    # ties: output lengths of 1 to 3, so that whole groups finish at one step (more of them than
+    # the prefills at hand), with thresholds where TTFT, TPOT and end-to-end flags are mixed
+    rng = np.random.default_rng(1000 * n + B + ties)
+    rows = 32768 + 77
+    q = random_queue(rng, n, max_in=2048, max_out=3 if ties else 400, thr_hi=200_000 if ties else 5_000_000)
+    m = Model(B, 1, p0=2000, p1=40, d0=8000, d1=300, d2=2)
+    p = _orders(rng, rows, n)
+    bad = [0, 63, 64, 65, 127, rows // 2, rows - 64, rows - 1]
+    _spoil(p, bad, rng)
+    dq, dp = sl.DeviceQueue.from_queue(q), sl.perms_to_device(p)
+    got = sl.sched_eval(dq, m, dp).cpu().numpy()
+    assert (got[bad] == -1).all()
+    want = np.concatenate([sl.sched_eval(dq, m, c.contiguous()).cpu().numpy() for c in dp.split(4096)])
+    assert np.array_equal(got, want)
+    some = rng.integers(0, rows, 128)
+    assert np.array_equal(got[some], orc.eval_rows(q, m, p[some]))
+
+
+@pytest.mark.parametrize("field,value", [("out", 5792), ("out", 5793), ("d0", (1 << 24) - 64), ("d0", 1 << 24),
+                                         ("thr", 0xFFFFFFFE), ("zero", 0)])
+def test_continuous_lanes_widths(sl, orc, field, value):
+    # both sides of the 24-bit factors; the largest threshold; a model whose every time is zero
+    rng = np.random.default_rng(value + 5)
+    n, B, rows = 20, 6, 16384
+    q = random_queue(rng, n, max_in=9, max_out=6, thr_hi=100_000_000)
+    m = Model(B, 1, p0=10, p1=1, d0=10, d1=3, d2=1)
+    if field == "out":
+        q.out_len[3] = value
+    elif field == "d0":
+        m.d0 = value
+    elif field == "thr":
+        q.thr_us[::2] = value
+    else:
+        m = Model(B, 1, p0=0, p1=0, d0=0, d1=0, d2=0)
+        q.thr_us[::2] = 0
+    p = _orders(rng, rows, n)
+    got = sl.sched_eval(sl.DeviceQueue.from_queue(q), m, sl.perms_to_device(p)).cpu().numpy()
+    some = np.arange(0, rows, 23)
+    assert np.array_equal(got[some], orc.eval_rows(q, m, p[some]))
