@@ -1,30 +1,30 @@
-// Continuous admission with two proposals scored per round (speculative pairs).
+// Continuous admission with several proposals scored per round (speculation).
 //
-// Algorithm 1 scores one proposal at a time against the current order. Proposal k + 1 is
-// scored against the same order whenever proposal k is rejected, so a round scores k and
-// k + 1 against the current order at once: if k is accepted, the score of k + 1 is dropped
-// and k + 1 is scored again in the next round against the new order; if k is rejected, the
-// score of k + 1 is exactly the one the chain needs. The trajectory, accept count, digest
-// and best order are those of scoring one proposal at a time, and a round completes two
-// proposals whenever the first is rejected.
+// Algorithm 1 scores one proposal at a time against the current order. Which order proposal
+// k + d meets depends only on which of the d proposals before it are kept, so a round scores
+// W proposals at once, one per wave of the chain's workgroup: wave 0 proposal k, every other
+// wave a later proposal under one assumed outcome of the ones before it (a node of the tree
+// of outcomes, kSpecTree). After a workgroup barrier all waves take the same decisions from
+// the scores, node by node, until an outcome was not assumed by any wave. The trajectory,
+// accept count, digest and best order are those of scoring one proposal at a time. The nodes
+// are the W most probable ones for the chain's recent rate of acceptance (a running mean).
 //
-// One workgroup of two waves per chain: wave w scores proposal k + w. The replay is the
-// list-scheduling one with 32-bit times (the running requests in a sliding window when at
-// most 32 run, else one pop per step from lane 0), restarted at the chunk of admissions
-// holding the candidate's first change; it is bound by the issue of its own serial steps,
-// so the second wave of a chain works in issue slots the SIMD would otherwise leave empty.
-// The waves meet once per round at the workgroup barrier, after which both take the same
-// decisions from the two scores, and once more when a move is accepted (the first wave
-// applies it to the shared records before either replays again).
+// The replay is the list-scheduling one with 32-bit times (the running requests in a sliding
+// window when at most 32 run, else one pop per step from lane 0), restarted at the chunk of
+// admissions holding the candidate's first change; it is bound by the latency and issue of
+// its own serial steps, so the further waves of a chain work in issue slots that the SIMDs
+// would otherwise leave empty. The waves meet once per round at the workgroup barrier, and
+// once more when a move is accepted (the first wave applies the moves to the shared records
+// before any wave replays again).
 //
-// Candidate records are read from the current order's records through a branch-free
-// position map, so one copy of them serves both waves. LDS per chain: those records
-// (16 B per position, request id above the kind bits), per wave five 32-bit arrays of
-// n + 1 entries (prefill prefix sums, run starts, run-end prefills, segment-cost prefix
-// sums, TTFTs), three sets of admission pops plus chunk-start keys (the current
-// order's and one per wave), and the two waves' scores in two slots used in alternate
-// rounds. The request table is not staged in LDS: each chain reads its start order's
-// records once from global memory.
+// Candidate records are read from the current order's records through a position map, so one
+// copy of them serves all waves. LDS per
+// chain: those records (16 B per position, request id above the kind bits), per wave four
+// 32-bit arrays of n + 1 entries (prefill prefix sums, run starts, run-end prefills,
+// segment-cost prefix sums, overwritten by the TTFTs), W + 1 sets of admission pops plus chunk-start keys (the
+// current order's and one per wave), and the waves' scores in two slots used in alternate
+// rounds. The request table is not staged in LDS: each chain reads its start order's records
+// once from global memory.
 #pragma once
 
 #include "kernels.h"
@@ -51,8 +51,8 @@ __device__ __forceinline__ SrcMap src_map(int kind, int i, int j) {
   return SrcMap{j, i, j + 1, -1, (uint32_t)(i - j)};
 }
 
-// one wave's five arrays of n + 1 entries
-__host__ __device__ __forceinline__ size_t spec_cand_bytes(int n) { return ((size_t)20 * (n + 1) + 15) / 16 * 16; }
+// one wave's four arrays of n + 1 entries
+__host__ __device__ __forceinline__ size_t spec_cand_bytes(int n) { return ((size_t)16 * (n + 1) + 15) / 16 * 16; }
 // Admissions per chunk and running keys kept per chunk start: with at most 32 running, the
 // sliding window's 64 - n0 admissions and 32 keys; with more, 64 admissions and n0 keys.
 __host__ __device__ __forceinline__ int spec_chunk_len(int n0) { return n0 <= 32 ? 64 - n0 : 64; }
@@ -64,56 +64,73 @@ __host__ __device__ __forceinline__ size_t spec_chunk_bytes(int n, int B) {
   return nadm > 0 ? (size_t)((nadm + S - 1) / S) * spec_snap_len(n0) * 4 : 0;
 }
 __host__ __device__ __forceinline__ size_t spec_pop_bytes(int n) { return ((size_t)4 * n + 15) / 16 * 16; }
-// scores exchanged per round: 2 slots x 2 waves x 32 B
-constexpr size_t kSpecXchBytes = 128;
-// LDS of one chain (one workgroup)
-__host__ __device__ __forceinline__ size_t spec_chain_bytes(int n, int B) {
-  return kSpecXchBytes + (size_t)16 * n + 2 * spec_cand_bytes(n) + 3 * (spec_pop_bytes(n) + spec_chunk_bytes(n, B));
+// Nodes of the tree of outcomes, most probable first: proposal depth << 8 | outcomes of the
+// proposals before it (bit d: proposal d kept), for acceptance rates around 0.1, 0.3, 0.5, 0.7
+// and 0.9. Every prefix of a row holds its own ancestors, so the first W serve W waves. Mean
+// proposals completed per round by 2, 4 and 8 waves: 1.9, 3.4 and 5.7 at 0.1 (and 0.9), 1.7, 2.5
+// and 3.5 at 0.3 (and 0.7), 1.5, 2.25 and 3.1 at 0.5.
+constexpr int kSpecWavesMax = 8;
+__device__ __constant__ const uint16_t kSpecTree[5][kSpecWavesMax] = {
+    {0x000, 0x100, 0x200, 0x300, 0x400, 0x500, 0x600, 0x700},
+    {0x000, 0x100, 0x200, 0x300, 0x101, 0x400, 0x201, 0x202},
+    {0x000, 0x100, 0x101, 0x200, 0x202, 0x201, 0x203, 0x300},
+    {0x000, 0x101, 0x203, 0x307, 0x100, 0x40f, 0x202, 0x201},
+    {0x000, 0x101, 0x203, 0x307, 0x40f, 0x51f, 0x63f, 0x77f}};
+
+// scores exchanged per round: 2 slots x W waves x 32 B
+__host__ __device__ __forceinline__ size_t spec_xch_bytes(int W) { return (size_t)64 * W; }
+// LDS of one chain (one workgroup of W waves)
+__host__ __device__ __forceinline__ size_t spec_chain_bytes(int n, int B, int W) {
+  return spec_xch_bytes(W) + (size_t)16 * n + W * spec_cand_bytes(n) +
+         (W + 1) * (spec_pop_bytes(n) + spec_chunk_bytes(n, B)) + (W > 2 ? (size_t)W * (((size_t)2 * n + 15) / 16 * 16) : 0);
 }
 
-// The current order's admission state: pops, chunk-start keys (whose first n0 entries are
-// the initial group's sorted keys whenever a request waits), the initial group's prefill
-// and context sums; and the buffers of the two waves' candidates. Accepting candidate C
-// swaps its buffers with the current ones. Both waves keep identical copies.
-struct SpecCache {
-  uint32_t *ev_cur, *snap_cur, *ev_c[2], *snap_c[2];
-  uint32_t pr0_cur, c1_cur;
-  template <int C>
-  __device__ __forceinline__ void accept(uint32_t pr0, uint32_t c1) {
-    uint32_t *t = ev_cur;
-    ev_cur = ev_c[C];
-    ev_c[C] = t;
-    t = snap_cur;
-    snap_cur = snap_c[C];
-    snap_c[C] = t;
-    pr0_cur = pr0;
-    c1_cur = c1;
-  }
+// Two waves: the second one's candidate may stand on the first one's move.
+struct SrcPair {
+  SrcMap own, under;
+  __device__ __forceinline__ int src(int p) const { return under.src(own.src(p)); }
+};
+// With more waves than two a candidate may stand on several moves: its positions map through
+// an index array of its own (one more LDS read per lookup; maps in registers, one per move,
+// cost seven instructions each and their scalars spill).
+struct SrcIndex {
+  const uint16_t *idx;
+  __device__ __forceinline__ int src(int p) const { return (int)idx[p]; }
+};
+
+// One order's admission state: pops and chunk-start keys (whose first n0 entries are the
+// initial group's sorted keys whenever a request waits), and the current order's initial
+// group's prefill and context sums.
+struct SpecCur {
+  const uint32_t *ev, *snap;
+  uint32_t pr0, c1;
 };
 
 // Score of one candidate of the current order. lo is the first position it changes:
 // admissions before the window chunk holding it are the current order's. ev and snap
-// receive the candidate's pops and chunk-start keys, sc holds its five arrays; pr0 and c1
+// receive the candidate's pops and chunk-start keys, sc holds its four arrays; pr0 and c1
 // receive its initial group's sums. Every time fits 32 bits (checked on the device before
 // the kernel runs).
-__device__ __forceinline__ Score spec_replay(const DevModel &m, const uint4 *__restrict__ posr, const SrcMap sm,
-                                             const int lo, const SpecCache &cc, uint32_t *ev, uint32_t *snap,
+template <class Map>
+__device__ __forceinline__ Score spec_replay(const DevModel &m, const uint4 *__restrict__ posr, const Map &sm,
+                                             const int lo, const SpecCur &cc, uint32_t *ev, uint32_t *snap,
                                              uint32_t *sc, uint32_t &pr0, uint32_t &c1) {
   const int lane = lane_id();
   const int N = m.n, B = m.B;
   const int n0 = min(B, N), nadm = N - n0;
   const uint32_t d0 = (uint32_t)m.d0, d1 = (uint32_t)m.d1, d2 = (uint32_t)m.d2;
-  const int W = N + 1;
-  uint32_t *preA = sc, *rsA = sc + W, *runpre = sc + 2 * W, *segA = sc + 3 * W, *tta = sc + 4 * W;
+  const int A = N + 1;
+  uint32_t *preA = sc, *rsA = sc + A, *runpre = sc + 2 * A, *segA = sc + 3 * A;
+  uint32_t *tta = segA;  // pass B leaves each event's TTFT in place of its segment-cost sum
   constexpr uint32_t kInf = 0xFFFFFFFFu;
 
   // initial group: positions 0 .. n0 - 1 start at step 0 (the current order's when the
   // candidate changes no position below n0)
   uint32_t list;
   if (lo >= n0) {
-    list = lane < n0 ? cc.snap_cur[lane] : kInf;
-    pr0 = cc.pr0_cur;
-    c1 = cc.c1_cur;
+    list = lane < n0 ? cc.snap[lane] : kInf;
+    pr0 = cc.pr0;
+    c1 = cc.c1;
   } else {
     uint32_t key = kInf, lin0 = 0, pf0 = 0;
     if (lane < n0) {
@@ -136,9 +153,9 @@ __device__ __forceinline__ Score spec_replay(const DevModel &m, const uint4 *__r
   const int Sfull = spec_chunk_len(n0), SN = spec_snap_len(n0);
   const int cr = lo >= n0 ? (lo - n0) / Sfull : 0;
   int done = min(cr * Sfull, nadm);
-  for (int x = lane; x < done; x += kWave) ev[x] = cc.ev_cur[x];
-  for (int x = lane; x < cr * SN; x += kWave) snap[x] = cc.snap_cur[x];
-  if (done > 0) list = lane < n0 ? cc.snap_cur[cr * SN + lane] : kInf;
+  for (int x = lane; x < done; x += kWave) ev[x] = cc.ev[x];
+  for (int x = lane; x < cr * SN; x += kWave) snap[x] = cc.snap[x];
+  if (done > 0) list = lane < n0 ? cc.snap[cr * SN + lane] : kInf;
   if (n0 > 32) {
     // More than 32 running: the sorted keys fill lanes [0, n0), kInf above; a step pops
     // lane 0 and leaves lane i = max(list[i], min(list[i + 1], nk)); the pops enter lane 0
@@ -258,35 +275,35 @@ __device__ __forceinline__ Score spec_replay(const DevModel &m, const uint4 *__r
   return Score{nmet, wave_sum_u64_dpp(tsum)};
 }
 
-// One workgroup of two waves per chain (blockDim 128, one chain per block).
-template <int OBJ>
-__global__ void __launch_bounds__(128) anneal_cont_spec_kernel(DevModel m, QueuePtrs q, int chains, int iters,
-                                                                double T0, double alpha, uint32_t key0, uint32_t key1,
-                                                                uint64_t swap_thr, SearchParams srch,
-                                                                unsigned char *ws) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  if (!gate_open(ws, m.gate, m.flags)) return;
+// One chain by one workgroup of W waves: record slot `chain`, Philox chain index `rng_chain`.
+template <int OBJ, int W>
+__device__ void anneal_cont_spec_body(const DevModel &m, const QueuePtrs &q, unsigned char *lds, int chains, int chain,
+                                      uint32_t rng_chain, int iters, double T0, double alpha, uint32_t key0,
+                                      uint32_t key1, uint64_t swap_thr, const SearchParams &srch, unsigned char *ws) {
   const int n = m.n;
-  const int chain = (int)blockIdx.x;
-  if (chain >= chains) return;
   const int w = uniform((int)(threadIdx.x >> 6));
   const int lane = lane_id();
-  // scores of the two waves, slot r & 1 in round r: {n, t, pr0 | c1 << 32, unused}
+  // scores of the waves, slot r & 1 in round r: {n, t, pr0 | c1 << 32, unused}
   uint64_t *xch = reinterpret_cast<uint64_t *>(lds);
-  uint4 *posr = reinterpret_cast<uint4 *>(lds + kSpecXchBytes);
-  unsigned char *base = lds + kSpecXchBytes + (size_t)16 * n;
+  uint4 *posr = reinterpret_cast<uint4 *>(lds + spec_xch_bytes(W));
+  unsigned char *base = lds + spec_xch_bytes(W) + (size_t)16 * n;
   uint32_t *sc = reinterpret_cast<uint32_t *>(base + (size_t)w * spec_cand_bytes(n));
-  SpecCache cc{};
-  {
-    unsigned char *cb = base + 2 * spec_cand_bytes(n);
-    const size_t evb = spec_pop_bytes(n), snb = spec_chunk_bytes(n, m.B);
-    cc.ev_cur = reinterpret_cast<uint32_t *>(cb);
-    cc.ev_c[0] = reinterpret_cast<uint32_t *>(cb + evb);
-    cc.ev_c[1] = reinterpret_cast<uint32_t *>(cb + 2 * evb);
-    cc.snap_cur = reinterpret_cast<uint32_t *>(cb + 3 * evb);
-    cc.snap_c[0] = reinterpret_cast<uint32_t *>(cb + 3 * evb + snb);
-    cc.snap_c[1] = reinterpret_cast<uint32_t *>(cb + 3 * evb + 2 * snb);
-  }
+  // W + 1 sets of pops and chunk-start keys: nibble w of `sets` is the set of wave w's
+  // candidate, nibble W the current order's; accepting a candidate exchanges the two
+  unsigned char *cb = base + W * spec_cand_bytes(n);
+  const size_t evb = spec_pop_bytes(n), snb = spec_chunk_bytes(n, m.B);
+  uint64_t sets = 0x876543210ull;
+  auto set_ev = [&](int s) { return reinterpret_cast<uint32_t *>(cb + (size_t)((sets >> (4 * s)) & 15u) * evb); };
+  auto set_snap = [&](int s) {
+    return reinterpret_cast<uint32_t *>(cb + (W + 1) * evb + (size_t)((sets >> (4 * s)) & 15u) * snb);
+  };
+  auto accept_set = [&](int s) {
+    const uint64_t x = ((sets >> (4 * s)) ^ (sets >> (4 * W))) & 15u;
+    sets ^= (x << (4 * s)) | (x << (4 * W));
+  };
+  uint16_t *idx = reinterpret_cast<uint16_t *>(cb + (W + 1) * (evb + snb) + (size_t)w * (((size_t)2 * n + 15) / 16 * 16));
+  if constexpr (W > 2)
+    for (int p = lane; p < n; p += kWave) idx[p] = (uint16_t)p;
   const WsHeader *h = reinterpret_cast<const WsHeader *>(ws);
   const int64_t t_ref = h->t_ref;
   int64_t cn = h->start_n;
@@ -297,7 +314,7 @@ __global__ void __launch_bounds__(128) anneal_cont_spec_kernel(DevModel m, Queue
   uint16_t *gbest = reinterpret_cast<uint16_t *>(ws + ws_off_best(n, chains)) + (size_t)chain * stride;
   uint16_t *gcur = reinterpret_cast<uint16_t *>(ws + ws_off_cur(n, chains)) + (size_t)chain * stride;
   // the start order's records by position, with the request id above the kind bits
-  for (int p = (int)threadIdx.x; p < n; p += 2 * kWave) {
+  for (int p = (int)threadIdx.x; p < n; p += W * kWave) {
     const uint16_t r = start[p];
     gbest[p] = r;
     const uint32_t lin = q.in_len[r], lout = q.out_len[r];
@@ -306,12 +323,11 @@ __global__ void __launch_bounds__(128) anneal_cont_spec_kernel(DevModel m, Queue
   }
   __syncthreads();
   // the start order's state: each wave replays it into its own buffers, the first wave's
-  // become the current ones (both waves compute the same sums)
+  // become the current ones (all waves compute the same sums)
+  uint32_t cur_pr0 = 0, cur_c1 = 0;
   {
-    uint32_t pr0, c1;
-    spec_replay(m, posr, src_map(0, 0, 0), 0, cc, w ? cc.ev_c[1] : cc.ev_c[0], w ? cc.snap_c[1] : cc.snap_c[0], sc,
-                pr0, c1);
-    cc.accept<0>(pr0, c1);
+    spec_replay(m, posr, src_map(0, 0, 0), 0, SpecCur{set_ev(W), set_snap(W), 0u, 0u}, set_ev(w), set_snap(w), sc, cur_pr0, cur_c1);
+    accept_set(0);
   }
   __syncthreads();
   int64_t bn = cn;
@@ -321,78 +337,112 @@ __global__ void __launch_bounds__(128) anneal_cont_spec_kernel(DevModel m, Queue
   Cooling cool{T0, alpha, srch.level_len, srch.level_len};
   ProposalStream ps;  // iterations kb .. kb + 63
   int kb = 0, slot = 0;
+  int rate = 3 << 14;  // running mean of the acceptances, of 2^16 (high at the start)
   const int iters_run = (srch.early_exit && allmet) ? 0 : iters;
-  if (iters_run > 0) ps.refill(0, lane, n, (uint32_t)chain, key0, key1, swap_thr, 0);
+  if (iters_run > 0) ps.refill(0, lane, n, rng_chain, key0, key1, swap_thr, 0);
   for (int k = 0; k < iters_run;) {
-    if (k + 1 - kb >= kWave) {
+    if (k + W - 1 - kb >= kWave) {
       kb = k;
-      ps.refill(kb, lane, n, (uint32_t)chain, key0, key1, swap_thr, 0);
+      ps.refill(kb, lane, n, rng_chain, key0, key1, swap_thr, 0);
     }
-    const bool two = k + 1 < iters_run;
-    const uint32_t pk0 = rl(ps.pk, k - kb), pk1 = rl(ps.pk, k + 1 - kb);
-    const int i0 = (int)(pk0 & 1023u), j0 = (int)((pk0 >> 10) & 1023u), t0 = (int)((pk0 >> 20) & 1u) + 1;
-    const int i1 = (int)(pk1 & 1023u), j1 = (int)((pk1 >> 10) & 1023u), t1 = (int)((pk1 >> 20) & 1u) + 1;
-    const int mi = w ? i1 : i0, mj = w ? j1 : j0, mt = w ? t1 : t0;
+    // two waves: proposals k and k + 1, the second on the current order or, when most
+    // proposals are accepted, on the first one's candidate
+    const bool on_acc = rate >= 1 << 15;
+    const uint16_t *tree = kSpecTree[W == 2 ? 0 : min((rate * 5) >> 16, 4)];
+    const SpecCur cc{set_ev(W), set_snap(W), cur_pr0, cur_c1};
     uint32_t pr0, c1;
-    // (the buffer pointers are selected, not indexed by the wave, which would place them in
-    // scratch memory)
-    uint32_t *my_ev = w ? cc.ev_c[1] : cc.ev_c[0], *my_snap = w ? cc.snap_c[1] : cc.snap_c[0];
-    const Score s = spec_replay(m, posr, src_map(mt, mi, mj), min(mi, mj), cc, my_ev, my_snap, sc, pr0, c1);
-    uint64_t *mine = xch + (slot * 2 + w) * 4;
+    Score s;
+    if constexpr (W == 2) {
+      auto map_of = [&](int d, int &lo) {
+        const uint32_t pk = rl(ps.pk, k + d - kb);
+        const int i = (int)(pk & 1023u), j = (int)((pk >> 10) & 1023u);
+        lo = min(i, j);
+        return src_map((int)((pk >> 20) & 1u) + 1, i, j);
+      };
+      int lo, lo0;
+      const SrcMap own = map_of(w, lo);
+      if (w == 1 && on_acc) {
+        const SrcMap under = map_of(0, lo0);
+        s = spec_replay(m, posr, SrcPair{own, under}, min(lo, lo0), cc, set_ev(w), set_snap(w), sc, pr0, c1);
+      } else {
+        s = spec_replay(m, posr, own, lo, cc, set_ev(w), set_snap(w), sc, pr0, c1);
+      }
+    } else {
+      // this wave's node: its proposal on top of the moves it assumes kept
+      const uint32_t node = (uint32_t)uniform((int)tree[w]);
+      const uint32_t mask = (node & 0xFFu) | (1u << (node >> 8));
+      int lo = n, hi = 0;
+      for (uint32_t left = mask; left; left &= left - 1) {
+        const uint32_t pk = rl(ps.pk, k + __builtin_ctz(left) - kb);
+        const int i = (int)(pk & 1023u), j = (int)((pk >> 10) & 1023u);
+        lo = min(lo, min(i, j));
+        hi = max(hi, max(i, j));
+        apply_move_lds(idx, i == j ? 0 : (int)((pk >> 20) & 1u) + 1, i, j, lane);
+      }
+      s = spec_replay(m, posr, SrcIndex{idx}, lo, cc, set_ev(w), set_snap(w), sc, pr0, c1);
+      for (int p = lo + lane; p <= hi; p += kWave) idx[p] = (uint16_t)p;
+    }
+    uint64_t *mine = xch + (slot * W + w) * 4;
     if (lane == 0) {
       mine[0] = (uint64_t)s.n;
       mine[1] = s.t;
       mine[2] = (uint64_t)pr0 | ((uint64_t)c1 << 32);
     }
     __syncthreads();
-    const uint64_t *x0 = xch + (slot * 2) * 4, *x1 = xch + (slot * 2 + 1) * 4;
-    const int64_t n0s = (int64_t)x0[0], n1s = (int64_t)x1[0];
-    const uint64_t t0s = x0[1], t1s = x1[1], g0 = x0[2], g1 = x1[2];
+    const uint64_t *x = xch + slot * W * 4;
     slot ^= 1;
-    int kacc = -1, ai = 0, aj = 0, at = 0;
-    if (obj_accept<OBJ>(cn, ct, n0s - cn, (int64_t)(t0s - ct), t_ref, cool.T, rl(ps.w3, k - kb))) {
+    int last = -1;  // the last accepted node
+    // decides proposal k, scored at `node`
+    auto decide = [&](int node) __attribute__((always_inline)) {
+      const int64_t sn = (int64_t)x[node * 4];
+      const uint64_t st = x[node * 4 + 1];
+      const bool acc = obj_accept<OBJ>(cn, ct, sn - cn, (int64_t)(st - ct), t_ref, cool.T, rl(ps.w3, k - kb));
       cool.step();
-      cc.accept<0>((uint32_t)g0, (uint32_t)(g0 >> 32));
-      kacc = k;
-      ai = i0;
-      aj = j0;
-      at = t0;
-      cn = n0s;
-      ct = t0s;
-      k += 1;
-    } else {
-      cool.step();
-      if (two) {
-        if (obj_accept<OBJ>(cn, ct, n1s - cn, (int64_t)(t1s - ct), t_ref, cool.T, rl(ps.w3, k + 1 - kb))) {
-          cc.accept<1>((uint32_t)g1, (uint32_t)(g1 >> 32));
-          kacc = k + 1;
-          ai = i1;
-          aj = j1;
-          at = t1;
-          cn = n1s;
-          ct = t1s;
+      rate += ((acc ? 1 << 16 : 0) - rate) >> 5;
+      if (acc) {
+        last = node;
+        cn = sn;
+        ct = st;
+        ++accepts;
+        digest = (digest ^ (uint64_t)k) * kFnvPrime;
+        digest = (digest ^ (uint64_t)cn) * kFnvPrime;
+        digest = (digest ^ ct) * kFnvPrime;
+        const bool better = obj_better<OBJ>(cn, ct, bn, bt);
+        if (better) {
+          bn = cn;
+          bt = ct;
+          biter = k;
         }
-        cool.step();
+        if (w == 0) {
+          const uint32_t pk = rl(ps.pk, k - kb);
+          const int i = (int)(pk & 1023u), j = (int)((pk >> 10) & 1023u);
+          apply_move_lds(posr, i == j ? 0 : (int)((pk >> 20) & 1u) + 1, i, j, lane);
+          if (better)
+            for (int p = lane; p < n; p += kWave) gbest[p] = (uint16_t)(posr[p].z >> 2);
+        }
       }
-      k += 2;
+      ++k;
+      return acc;
+    };
+    if constexpr (W == 2) {
+      if (decide(0) == on_acc && k < iters_run) decide(1);
+    } else {
+      uint32_t pattern = 0;  // outcomes so far in this round
+      for (int d = 0, node = 0; node >= 0; ++d) {
+        pattern |= decide(node) ? 1u << d : 0u;
+        if (k >= iters_run) break;
+        const uint32_t next = ((uint32_t)(d + 1) << 8) | pattern;
+        node = -1;
+#pragma unroll
+        for (int u = 1; u < W; ++u)
+          if ((uint32_t)uniform((int)tree[u]) == next) node = u;
+      }
     }
-    if (kacc >= 0) {
-      ++accepts;
-      digest = (digest ^ (uint64_t)kacc) * kFnvPrime;
-      digest = (digest ^ (uint64_t)cn) * kFnvPrime;
-      digest = (digest ^ ct) * kFnvPrime;
-      const bool better = obj_better<OBJ>(cn, ct, bn, bt);
-      if (better) {
-        bn = cn;
-        bt = ct;
-        biter = kacc;
-      }
-      if (w == 0) {
-        apply_move_lds(posr, ai == aj ? 0 : at, ai, aj, lane);
-        if (better)
-          for (int p = lane; p < n; p += kWave) gbest[p] = (uint16_t)(posr[p].z >> 2);
-      }
-      // both waves take this branch: the records change before either replays again
+    if (last >= 0) {
+      cur_pr0 = (uint32_t)x[last * 4 + 2];
+      cur_c1 = (uint32_t)(x[last * 4 + 2] >> 32);
+      accept_set(last);
+      // every wave takes this branch: the records change before any replays again
       __syncthreads();
     }
   }
@@ -410,6 +460,20 @@ __global__ void __launch_bounds__(128) anneal_cont_spec_kernel(DevModel m, Queue
       rec[7] = allmet;
     }
   }
+}
+
+// One workgroup of W waves per chain.
+template <int OBJ, int W>
+__global__ void __launch_bounds__(W * kWave) anneal_cont_spec_kernel(DevModel m, QueuePtrs q, int chains, int iters,
+                                                                      double T0, double alpha, uint32_t key0,
+                                                                      uint32_t key1, uint64_t swap_thr,
+                                                                      SearchParams srch, unsigned char *ws) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  if (!gate_open(ws, m.gate, m.flags)) return;
+  const int chain = (int)blockIdx.x;
+  if (chain >= chains) return;
+  anneal_cont_spec_body<OBJ, W>(m, q, lds, chains, chain, (uint32_t)chain, iters, T0, alpha, key0, key1, swap_thr, srch,
+                                ws);
 }
 
 }  // namespace sa

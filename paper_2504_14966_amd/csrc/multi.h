@@ -21,6 +21,7 @@
 // out for the instance's request count (so the single-queue readouts work on it), followed
 // by the instance's queue (structure of arrays) and the global ids of its requests.
 #pragma once
+#include "anneal_cont_spec.h"
 #include "anneal_reg.h"
 #include "anneal_static.h"
 #include "anneal_wave.h"
@@ -332,6 +333,27 @@ __global__ void __launch_bounds__(kBlock) multi_anneal_kernel(DevModel m, int n,
   if (chain >= chains) return;
   anneal_chain_body<OBJ>(mk, req, wbase, chains, chain, (uint32_t)(k * chains + chain), iters, T0, alpha, key0, key1,
                          swap_thr, srch, slot);
+}
+
+// Continuous admission by list scheduling with 32-bit times, W proposals per round (one
+// workgroup of W waves per chain, block k * chains + chain); LDS for the largest instance the
+// launch may meet, laid out for the block's own.
+template <int OBJ, int W>
+__global__ void __launch_bounds__(W * kWave) multi_cont_spec_kernel(DevModel m, int n, int instances, int chains,
+                                                                     int iters, double T0, double alpha, uint32_t key0,
+                                                                     uint32_t key1, uint64_t swap_thr,
+                                                                     SearchParams srch, unsigned char *mws) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  if (!gate_open(mws, m.gate, m.flags)) return;
+  const int k = blockIdx.x / chains, chain = blockIdx.x - k * chains;
+  const int nk = slot_n(mws, k);
+  if (nk == 0) return;
+  unsigned char *slot = mws + mws_off_slot(n, instances, chains, k);
+  const SlotQueue sq = slot_queue(slot, n, chains);
+  DevModel mk = m;
+  mk.n = nk;
+  anneal_cont_spec_body<OBJ, W>(mk, QueuePtrs{sq.in_len, sq.out_len, sq.kind, sq.thr}, lds, chains, chain,
+                                (uint32_t)(k * chains + chain), iters, T0, alpha, key0, key1, swap_thr, srch, slot);
 }
 
 // Static admission with the delta kernels: instances x groups of `waves` chains, one wave per

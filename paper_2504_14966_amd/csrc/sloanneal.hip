@@ -110,7 +110,7 @@ struct Candidates {
   uint32_t allow[4] = {0u, 0u, 0u, 0u};
   std::function<hipError_t(const M &)> launch[4];
   void add(uint32_t need, uint32_t allow_flags, std::function<hipError_t(const M &)> fn) {
-    if (gate.count >= 4) return;  // at most three per call by construction
+    if (gate.count >= 4) return;  // at most four per call by construction
     gate.need[gate.count] = need;
     allow[gate.count] = allow_flags;
     launch[gate.count] = std::move(fn);
@@ -342,6 +342,64 @@ hipError_t launch_static(int waves, size_t lds, const sa::DevModel &d, const sa:
   return hipGetLastError();
 }
 
+// Continuous admission with several proposals scored per round, one wave each (list
+// scheduling, 32-bit times). Two waves per chain when at least as many chains fit on a CU at
+// once as under the single-proposal list-scheduling kernel; more when the chains leave the
+// GPU so empty that the SIMDs still hold at most two waves (256 requests, 32 running, 52 % of the
+// proposals accepted, two / four / eight waves: 256 chains 8.2 / 6.4 / 5.4 ms, 512 chains 8.4 /
+// 7.0 / 7.0 ms, 1024 chains 8.7 / 9.2 / 13.1 ms). `any`: two waves whenever they fit at all.
+template <int OBJ>
+int spec_waves(int n, int B, int chains, bool any = false) {
+  const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
+  auto resident = [&](const void *fn, int W) {  // workgroups the GPU holds at once
+    const size_t lds = sa::spec_chain_bytes(n, B, W);
+    int nb = 0;
+    if (lds > (size_t)lim ||
+        (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, W * 64, lds) != hipSuccess)
+      nb = 0;
+    return (int64_t)nb * cus;
+  };
+  if (chains <= cus && resident((const void *)&sa::anneal_cont_spec_kernel<OBJ, 8>, 8) >= chains) return 8;
+  if (chains <= 2 * cus && resident((const void *)&sa::anneal_cont_spec_kernel<OBJ, 4>, 4) >= chains) return 4;
+  const int64_t res2 = resident((const void *)&sa::anneal_cont_spec_kernel<OBJ, 2>, 2);
+  if (any) return res2 > 0 ? 2 : 0;
+  int w1 = 1;
+  while (w1 < 16 && (int64_t)w1 * cus < chains) w1 <<= 1;
+  const size_t per1 = (((size_t)n * 2 + 15) & ~size_t(15)) + ((sa::cont_ls_scratch_bytes(n) + 15) & ~size_t(15)) +
+                      (std::min(B, n) <= 32 ? sa::cont_inc_bytes(n, B) : 0);
+  while (w1 > 1 && (size_t)n * 16 + per1 * w1 > (size_t)lim) w1 >>= 1;
+  const size_t lds1 = (size_t)n * 16 + per1 * w1;
+  const int64_t res1 = lds1 <= (size_t)lim ? (int64_t)w1 * std::max<int64_t>(1, lim / (int64_t)lds1) : 0;
+  return res2 > 0 && std::min<int64_t>(chains, res2) >= std::min<int64_t>(chains, res1 * cus) ? 2 : 0;
+}
+
+template <int OBJ, int W>
+hipError_t launch_cont_spec(size_t lds, const sa::DevModel &d, const ChainArgs &a) {
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sa::anneal_cont_spec_kernel<OBJ, W>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  sa::anneal_cont_spec_kernel<OBJ, W><<<a.chains, W * 64, lds, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha,
+                                                                          a.k0, a.k1, a.swap_thr, a.srch, a.w);
+  return hipGetLastError();
+}
+
+template <int OBJ>
+void add_cont_spec(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const ChainArgs &a) {
+  const int W = spec_waves<OBJ>(n, model->max_batch, a.chains);
+  if (W == 0) return;
+  const size_t lds = sa::spec_chain_bytes(n, model->max_batch, W);
+  c.add(sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime, kAnnealFlags, [=](const sa::DevModel &d) {
+    switch (W) {
+      case 8: return launch_cont_spec<OBJ, 8>(lds, d, a);
+      case 4: return launch_cont_spec<OBJ, 4>(lds, d, a);
+      default: return launch_cont_spec<OBJ, 2>(lds, d, a);
+    }
+  });
+}
+
 // The kernels a single-queue sched_anneal may run, by policy, in order of preference:
 //   static: the register kernel (up to 64 requests, or 65 to 192 with two or three positions
 //     per lane; batches of 1 .. 16, a power of two) or else the LDS delta kernel (one lane per
@@ -418,34 +476,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
     }
   }
   if (model->policy == SCHED_CONTINUOUS) {
-    // Two proposals scored per round by two waves of one workgroup per chain (list
-    // scheduling, 32-bit times), when at least as many chains fit on a CU at once as under
-    // the single-proposal list-scheduling kernel.
-    {
-      const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
-      int w1 = 1;
-      while (w1 < 16 && (int64_t)w1 * cus < a.chains) w1 <<= 1;
-      const size_t per1 = (((size_t)n * 2 + 15) & ~size_t(15)) + ((sa::cont_ls_scratch_bytes(n) + 15) & ~size_t(15)) +
-                          (std::min(B, n) <= 32 ? sa::cont_inc_bytes(n, B) : 0);
-      while (w1 > 1 && (size_t)n * 16 + per1 * w1 > (size_t)lim) w1 >>= 1;
-      const size_t lds1 = (size_t)n * 16 + per1 * w1;
-      const int64_t res1 = lds1 <= (size_t)lim ? (int64_t)w1 * std::max<int64_t>(1, lim / (int64_t)lds1) : 0;
-      const size_t lds = sa::spec_chain_bytes(n, B);
-      const void *fn = (const void *)&sa::anneal_cont_spec_kernel<OBJ>;
-      int nb = 0;
-      if (lds > (size_t)lim ||
-          (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) ||
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 128, lds) != hipSuccess)
-        nb = 0;
-      if (nb > 0 && std::min<int64_t>(a.chains, (int64_t)nb * cus) >= std::min<int64_t>(a.chains, res1 * cus)) {
-        c.add(sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime, kAnnealFlags,
-              [=](const sa::DevModel &d) {
-                sa::anneal_cont_spec_kernel<OBJ><<<a.chains, 128, lds, a.stream>>>(
-                    d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0, a.k1, a.swap_thr, a.srch, a.w);
-                return hipGetLastError();
-              });
-      }
-    }
+    add_cont_spec<OBJ>(c, model, n, a);
     for (int ls = 1; ls >= 0; --ls) {
       const size_t soa = (size_t)n * 16;
       const bool inc = ls && std::min(B, n) <= 32;
@@ -524,7 +555,20 @@ hipError_t launch_multi_static(int grid, int waves, int groups, size_t lds, cons
   return hipGetLastError();
 }
 
-// The kernels a sched_anneal_multi may run, in order of preference (static admission):
+template <int OBJ, int W>
+hipError_t launch_multi_cont(size_t lds, const sa::DevModel &d, const MultiArgs &a) {
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sa::multi_cont_spec_kernel<OBJ, W>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  sa::multi_cont_spec_kernel<OBJ, W><<<a.instances * a.chains, W * 64, lds, a.stream>>>(
+      d, a.n, a.instances, a.chains, a.iters, a.T0, a.alpha, a.k0, a.k1, a.swap_thr, a.srch, a.w);
+  return hipGetLastError();
+}
+
+// The kernels a sched_anneal_multi may run, in order of preference. Continuous admission: list
+// scheduling by the most requests an instance holds, else the full-replay kernel. Static:
 // the register kernel when every instance holds at most 64 requests, its two- and
 // three-position form when every instance holds at most 192 (batches of 1 .. 16, a power of
 // two, on the 32-bit pair-cost widths); the LDS delta kernels, laid out for the whole queue
@@ -571,6 +615,26 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
           case 4: return launch_multi_static<4, OBJ>(grid, waves, groups, lds, d, sp, a);
           case 5: return launch_multi_static<5, OBJ>(grid, waves, groups, lds, d, sp, a);
           default: return launch_multi_static<6, OBJ>(grid, waves, groups, lds, d, sp, a);
+        }
+      });
+    }
+  }
+  if (model->policy == SCHED_CONTINUOUS) {
+    // list scheduling, 32-bit times: LDS for instances of at most 64 or 192 requests, or of
+    // the whole queue (more waves per chain when the chains leave the GPU nearly empty)
+    const uint32_t need = sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime;
+    const int caps[3] = {64, 192, n};
+    const uint32_t bound[3] = {sa::kFlagInst64, sa::kFlagInst192, 0u};
+    for (int u = 0; u < 3; ++u) {
+      if (u < 2 && caps[u] >= n) continue;  // the last one covers the queue
+      const int W = spec_waves<OBJ>(caps[u], B, total, true);
+      if (W == 0) continue;
+      const size_t lds = sa::spec_chain_bytes(caps[u], B, W);
+      c.add(need | bound[u], kMultiFlags, [=](const sa::DevModel &d) {
+        switch (W) {
+          case 8: return launch_multi_cont<OBJ, 8>(lds, d, a);
+          case 4: return launch_multi_cont<OBJ, 4>(lds, d, a);
+          default: return launch_multi_cont<OBJ, 2>(lds, d, a);
         }
       });
     }
