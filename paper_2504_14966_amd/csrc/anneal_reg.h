@@ -1,10 +1,9 @@
 // Annealing chains under static admission for small queues, state in registers (gfx950).
 //
-// For at most 64 requests and a batch size of 1, 2, 4, 8 or 16, lane p holds the request at
-// position p of the order: its output length and id, its pair-cost parameter e = 2 (d1 + d2
+// For at most 64 requests, lane p holds the request at position p of the order: its output length and id, its pair-cost parameter e = 2 (d1 + d2
 // l_in) + d2 and kind, its prefill and its SLO threshold (for TPOT, threshold times output
-// length, saturated at 2^32 - 1). Batch k is lanes [kB, kB + B), inside one DPP row. A
-// proposal builds the candidate order in registers (a swap is two v_readlane and two
+// length, saturated at 2^32 - 1). For batches of 1, 2, 4, 8 or 16, batch k is lanes
+// [kB, kB + B), inside one DPP row (other sizes: kRegAny). A proposal builds the candidate order in registers (a swap is two v_readlane and two
 // v_writelane per field; an insert is one DPP wave shift, a range select and one
 // v_writelane) and replays it in full with no LDS traffic:
 //   - each member's finish offset F = P + L d0 + (sum over the batch's members j of
@@ -25,9 +24,12 @@
 
 namespace sa {
 
-// The small-queue kernel's applicability: n <= 64 and B a power of two up to 16.
-__host__ __device__ __forceinline__ bool reg_kernel_fits(int n, int B) {
-  return n >= 1 && n <= 64 && B >= 1 && B <= 16 && (B & (B - 1)) == 0;
+// The small-queue kernel's form for batches of B: log2 B for the powers of two up to 16, whose
+// batches are reached by row rotations; kRegAny for the others (members gathered with
+// ds_bpermute as in the batch-size search kernel, the batch bounds fixed per lane).
+constexpr int kRegAny = -1;
+__host__ __device__ __forceinline__ int reg_form(int B) {
+  return B == 1 ? 0 : (B == 2 ? 1 : (B == 4 ? 2 : (B == 8 ? 3 : (B == 16 ? 4 : kRegAny))));
 }
 
 template <int CTRL>
@@ -150,6 +152,86 @@ __device__ __forceinline__ Score reg_replay(const RegState &s, int n, uint32_t d
   }
 }
 
+__device__ __forceinline__ uint32_t bperm(uint32_t v, int src) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
+}
+
+// Pair terms of W consecutive members of the lane's batch from offset d: all 2W ds_bpermute
+// are in flight before their results are used.
+template <int W>
+__device__ __forceinline__ uint32_t pair_round(uint32_t L, uint32_t e, uint32_t d2, int b0, int bl, int d,
+                                               uint32_t acc) {
+  uint32_t Lj[W], ej[W];
+#pragma unroll
+  for (int u = 0; u < W; ++u) {
+    const int src = min(b0 + d + u, kWave - 1);
+    Lj[u] = bperm(L, src);
+    ej[u] = bperm(e, src);
+  }
+#pragma unroll
+  for (int u = 0; u < W; ++u) {
+    const uint32_t mu = min(Lj[u], L);
+    const uint32_t w = mad24_v(mu, mad24_v(d2, mu, ej[u]), 0u);
+    acc += d + u < bl ? w : 0u;
+  }
+  return acc;
+}
+
+// Full replay of the order in registers with the batches given per lane by their first and
+// last positions b0 <= lane <= b1 (lanes at or above n: b0 = b1 = lane), every batch at most
+// maxb long: (met count, total latency). A member's TTFT is the sum of the prefills of every
+// position up to its batch's end plus the decode durations of the earlier batches; its e2e
+// adds its own decode time G after the batch prefill. Prefills, G and batch durations fit
+// 32 bits (the host's width checks); the timeline need not: its prefix sums saturate at
+// 2^32 - 1, which no threshold reaches, and the total latency is formed exactly as the sum of
+// G, of each prefill times the requests from its batch's start onward and of each batch's
+// decode duration times the requests after it.
+// SAT = false: the whole timeline fits 32 bits (the host's check) and plain 32-bit scans do.
+template <bool SAT>
+__device__ __forceinline__ Score reg_replay_sized(const RegState &s, int b0, int b1, int maxb, int n, uint32_t d0,
+                                                  uint32_t d2, int lane) {
+  const bool valid = lane < n;
+  const uint32_t L = s.A & 0xFFFFu, e = s.E & 0x3FFFFFFFu, kind = s.E >> 30;
+  const int bl = b1 - b0 + 1;
+  // prefills up to the batch's end: one add-scan read at the batch's last lane (the gather
+  // is unconditional: ds_bpermute reads only lanes that execute it)
+  const uint32_t pend = bperm(SAT ? scan_add_sat32(s.PF) : scan_add32(s.PF), b1);
+  // pair terms: one round of gathers for batches of up to 8 (16 per round above)
+  uint32_t acc = 0;
+  if (maxb <= 8) {
+    acc = pair_round<8>(L, e, d2, b0, bl, 0, 0u);
+  } else {
+    for (int d = 0; d < maxb; d += 16) acc = pair_round<16>(L, e, d2, b0, bl, d, acc);
+  }
+  const uint32_t G = valid ? __umul24(L, d0) + (acc >> 1) : 0u;
+  // the batch's decode duration at its last lane
+  const uint32_t D = seg_max32(G, b0, b1, lane);
+  const bool last = valid && lane == b1;
+  const uint32_t contrib = last ? D : 0u;
+  uint32_t ttft, e2e, lo, hi;
+  if constexpr (SAT) {
+    // decode durations of the earlier batches: the inclusive scan moved up one lane
+    const uint32_t SD =
+        scan_add_sat32((uint32_t)__builtin_amdgcn_update_dpp(0, (int)contrib, kDppWaveShr1, 0xF, 0xF, false));
+    ttft = add_sat(pend, SD);
+    e2e = add_sat(ttft, G);
+    // the latency sum in 16-bit halves (each lane below 2^23, each sum below 2^29)
+    const uint32_t from = valid ? (uint32_t)(n - b0) : 0u, after = last ? (uint32_t)(n - 1 - b1) : 0u;
+    lo = (G & 0xFFFFu) + (s.PF & 0xFFFFu) * from + (contrib & 0xFFFFu) * after;
+    hi = (G >> 16) + (s.PF >> 16) * from + (contrib >> 16) * after;
+  } else {
+    ttft = pend + scan_add32(contrib) - contrib;
+    e2e = ttft + G;
+    // the latency sum: 16-bit halves of the 32-bit latencies, each sum below 2^22
+    lo = valid ? (e2e & 0xFFFFu) : 0u;
+    hi = valid ? (e2e >> 16) : 0u;
+  }
+  const bool met = valid && (kind == 0 ? ttft <= s.T : (kind == 2 ? e2e <= s.T : G <= s.T));
+  const int64_t nmet = __popcll(__ballot(met));
+  wave_all2<OpAdd, OpAdd>(lo, hi);
+  return Score{nmet, (uint64_t)lo + ((uint64_t)hi << 16)};
+}
+
 // One chain by one wave: record slot `chain`, Philox chain index `rng_chain`.
 template <int LG, int OBJ, bool T32>
 __device__ void anneal_reg_body(const DevModel &m, const QueuePtrs &q, int chains, int chain, uint32_t rng_chain,
@@ -177,7 +259,22 @@ __device__ void anneal_reg_body(const DevModel &m, const QueuePtrs &q, int chain
     cur.T = kind == 1 ? (uint32_t)min(thr_l, (uint64_t)0xFFFFFFFFu) : thr;
     gbest[lane] = (uint16_t)r;
   }
-  const Score s0 = reg_replay<LG, T32>(cur, n, d0, d2, lane);
+  // batches of any other size: the lane's batch bounds, and p / B
+  const int B = m.B, b0 = lane < n ? lane / B * B : lane, b1 = lane < n ? min(b0 + B, n) - 1 : lane;
+  const uint32_t bmagic = 65536u / (uint32_t)B + 1u;  // exact for p < 64, B <= 64
+  auto replay = [&](const RegState &s) __attribute__((always_inline)) {
+    if constexpr (LG == kRegAny)
+      return reg_replay_sized<!T32>(s, b0, b1, min(B, n), n, d0, d2, lane);
+    else
+      return reg_replay<LG, T32>(s, n, d0, d2, lane);
+  };
+  auto batch_of = [&](int p) {
+    if constexpr (LG == kRegAny)
+      return (int)(((uint32_t)p * bmagic) >> 16);
+    else
+      return p >> LG;
+  };
+  const Score s0 = replay(cur);
   int64_t cn = s0.n;
   uint64_t ct = s0.t;
   int64_t bn = cn;
@@ -197,7 +294,7 @@ __device__ void anneal_reg_body(const DevModel &m, const QueuePtrs &q, int chain
     const RegState cand{from_lane(addr, cur.A), from_lane(addr, cur.E), from_lane(addr, cur.PF), from_lane(addr, cur.T)};
     // a move inside one batch keeps every batch's members: the score is unchanged (and the
     // move is kept under either objective), so the replay is skipped
-    const Score s = (i >> LG) == (j >> LG) ? Score{cn, ct} : reg_replay<LG, T32>(cand, n, d0, d2, lane);
+    const Score s = batch_of(i) == batch_of(j) ? Score{cn, ct} : replay(cand);
     const bool acc = obj_accept<OBJ>(cn, ct, s.n - cn, (int64_t)(s.t - ct), t_ref, cool.T, w3);
     if (acc) {
       cur = cand;
@@ -575,86 +672,6 @@ __device__ __forceinline__ RegMove reg_plan(uint64_t fm, int n, int B, int op, i
   mv.set0 = e - 1;
   mv.clr0 = e;
   return mv;
-}
-
-__device__ __forceinline__ uint32_t bperm(uint32_t v, int src) {
-  return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
-}
-
-// Pair terms of W consecutive members of the lane's batch from offset d: all 2W ds_bpermute
-// are in flight before their results are used.
-template <int W>
-__device__ __forceinline__ uint32_t pair_round(uint32_t L, uint32_t e, uint32_t d2, int b0, int bl, int d,
-                                               uint32_t acc) {
-  uint32_t Lj[W], ej[W];
-#pragma unroll
-  for (int u = 0; u < W; ++u) {
-    const int src = min(b0 + d + u, kWave - 1);
-    Lj[u] = bperm(L, src);
-    ej[u] = bperm(e, src);
-  }
-#pragma unroll
-  for (int u = 0; u < W; ++u) {
-    const uint32_t mu = min(Lj[u], L);
-    const uint32_t w = mad24_v(mu, mad24_v(d2, mu, ej[u]), 0u);
-    acc += d + u < bl ? w : 0u;
-  }
-  return acc;
-}
-
-// Full replay of the order in registers with the batches given per lane by their first and
-// last positions b0 <= lane <= b1 (lanes at or above n: b0 = b1 = lane), every batch at most
-// maxb long: (met count, total latency). A member's TTFT is the sum of the prefills of every
-// position up to its batch's end plus the decode durations of the earlier batches; its e2e
-// adds its own decode time G after the batch prefill. Prefills, G and batch durations fit
-// 32 bits (the host's width checks); the timeline need not: its prefix sums saturate at
-// 2^32 - 1, which no threshold reaches, and the total latency is formed exactly as the sum of
-// G, of each prefill times the requests from its batch's start onward and of each batch's
-// decode duration times the requests after it.
-// SAT = false: the whole timeline fits 32 bits (the host's check) and plain 32-bit scans do.
-template <bool SAT>
-__device__ __forceinline__ Score reg_replay_sized(const RegState &s, int b0, int b1, int maxb, int n, uint32_t d0,
-                                                  uint32_t d2, int lane) {
-  const bool valid = lane < n;
-  const uint32_t L = s.A & 0xFFFFu, e = s.E & 0x3FFFFFFFu, kind = s.E >> 30;
-  const int bl = b1 - b0 + 1;
-  // prefills up to the batch's end: one add-scan read at the batch's last lane (the gather
-  // is unconditional: ds_bpermute reads only lanes that execute it)
-  const uint32_t pend = bperm(SAT ? scan_add_sat32(s.PF) : scan_add32(s.PF), b1);
-  // pair terms: one round of gathers for batches of up to 8 (16 per round above)
-  uint32_t acc = 0;
-  if (maxb <= 8) {
-    acc = pair_round<8>(L, e, d2, b0, bl, 0, 0u);
-  } else {
-    for (int d = 0; d < maxb; d += 16) acc = pair_round<16>(L, e, d2, b0, bl, d, acc);
-  }
-  const uint32_t G = valid ? __umul24(L, d0) + (acc >> 1) : 0u;
-  // the batch's decode duration at its last lane
-  const uint32_t D = seg_max32(G, b0, b1, lane);
-  const bool last = valid && lane == b1;
-  const uint32_t contrib = last ? D : 0u;
-  uint32_t ttft, e2e, lo, hi;
-  if constexpr (SAT) {
-    // decode durations of the earlier batches: the inclusive scan moved up one lane
-    const uint32_t SD =
-        scan_add_sat32((uint32_t)__builtin_amdgcn_update_dpp(0, (int)contrib, kDppWaveShr1, 0xF, 0xF, false));
-    ttft = add_sat(pend, SD);
-    e2e = add_sat(ttft, G);
-    // the latency sum in 16-bit halves (each lane below 2^23, each sum below 2^29)
-    const uint32_t from = valid ? (uint32_t)(n - b0) : 0u, after = last ? (uint32_t)(n - 1 - b1) : 0u;
-    lo = (G & 0xFFFFu) + (s.PF & 0xFFFFu) * from + (contrib & 0xFFFFu) * after;
-    hi = (G >> 16) + (s.PF >> 16) * from + (contrib >> 16) * after;
-  } else {
-    ttft = pend + scan_add32(contrib) - contrib;
-    e2e = ttft + G;
-    // the latency sum: 16-bit halves of the 32-bit latencies, each sum below 2^22
-    lo = valid ? (e2e & 0xFFFFu) : 0u;
-    hi = valid ? (e2e >> 16) : 0u;
-  }
-  const bool met = valid && (kind == 0 ? ttft <= s.T : (kind == 2 ? e2e <= s.T : G <= s.T));
-  const int64_t nmet = __popcll(__ballot(met));
-  wave_all2<OpAdd, OpAdd>(lo, hi);
-  return Score{nmet, (uint64_t)lo + ((uint64_t)hi << 16)};
 }
 
 template <int OBJ, bool SAT>

@@ -392,8 +392,8 @@ __global__ void __launch_bounds__(1024) multi_static_kernel(DevModel m, StaticPa
                                 srch, slot);
 }
 
-// Static admission on instances of at most 64 requests and batches of 1, 2, 4, 8 or 16: the
-// register kernel's chain body per instance (block k / groups), no LDS.
+// Static admission on instances of at most 64 requests: the register kernel's chain body per
+// instance (block k / groups), no LDS.
 template <int LG, int OBJ>
 __global__ void __launch_bounds__(256) multi_reg_kernel(DevModel m, int n, int instances, int chains, int groups,
                                                          int iters, double T0, double alpha, uint32_t key0,

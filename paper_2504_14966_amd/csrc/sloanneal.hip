@@ -218,6 +218,13 @@ size_t anneal_lds_bytes(int n) {
   return ((size_t)n * 16 + 15) / 16 * 16 + per_wave * sa::kWavesPerBlock;
 }
 
+// Whether the register kernel's form for any batch size beats the LDS delta kernels: its cost
+// grows with the batch (two lane gathers per member: 64 requests in batches of 3 take 2.6 ms
+// against 6.0 ms, of 24 1.27 against 1.94 ms, of 33 1.31 against 1.27 ms), and when one batch
+// holds every request no proposal needs a replay and neither wins (with several instances the
+// mean size decides: 3500 chains on instances of 6 in batches of 9, 494 against 443 us).
+bool reg_any_pays(int n, int B) { return B <= 32 && n > B; }
+
 // Chains per workgroup of the register kernels: four, or fewer so that the chains spread
 // over every CU.
 int reg_waves(int chains) {
@@ -301,11 +308,14 @@ void add_sized(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, c
 
 template <int LG, int OBJ>
 hipError_t launch_reg(bool parts, int grid, int waves, const sa::DevModel &d, const ChainArgs &a) {
-  if (parts)
-    sa::anneal_reg_h_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0,
-                                                                        a.k1, a.swap_thr, a.srch, a.w);
-  else
-    sa::anneal_reg_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0,
+  if constexpr (LG >= 0) {
+    if (parts) {
+      sa::anneal_reg_h_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha,
+                                                                          a.k0, a.k1, a.swap_thr, a.srch, a.w);
+      return hipGetLastError();
+    }
+  }
+  sa::anneal_reg_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0,
                                                                       a.k1, a.swap_thr, a.srch, a.w);
   return hipGetLastError();
 }
@@ -401,8 +411,8 @@ void add_cont_spec(Candidates<sa::DevModel> &c, const sched_model_t *model, int 
 }
 
 // The kernels a single-queue sched_anneal may run, by policy, in order of preference:
-//   static: the register kernel (up to 64 requests, or 65 to 192 with two or three positions
-//     per lane; batches of 1 .. 16, a power of two) or else the LDS delta kernel (one lane per
+//   static: the register kernel (up to 64 requests and batches up to 32; 65 to 192 with two or
+//     three positions per lane and batches of 1 .. 16, a power of two) or else the LDS delta kernel (one lane per
 //     batch member, or one batch per wave for batches of more than 32), both on the 32-bit
 //     pair-cost widths, the register kernel also on a 32-bit timeline when it holds, and
 //     one batch per wave with the members' SLO limits in registers ahead of the plain one
@@ -418,16 +428,17 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
     return;
   }
   if (model->policy == SCHED_STATIC) {
-    if (sa::reg_kernel_fits(n, B) || sa::reg_parts(n, B) > 1) {
-      const bool parts = !sa::reg_kernel_fits(n, B);
+    if ((n <= 64 && (sa::reg_form(B) != sa::kRegAny || reg_any_pays(n, B))) || sa::reg_parts(n, B) > 1) {
+      const bool parts = n > 64;
       const int waves = reg_waves(a.chains), grid = (a.chains + waves - 1) / waves;
       c.add(kSN, kAnnealFlags | kT32, [=](const sa::DevModel &d) {
-        switch (B) {
-          case 1: return launch_reg<0, OBJ>(parts, grid, waves, d, a);
-          case 2: return launch_reg<1, OBJ>(parts, grid, waves, d, a);
-          case 4: return launch_reg<2, OBJ>(parts, grid, waves, d, a);
-          case 8: return launch_reg<3, OBJ>(parts, grid, waves, d, a);
-          default: return launch_reg<4, OBJ>(parts, grid, waves, d, a);
+        switch (sa::reg_form(B)) {
+          case 0: return launch_reg<0, OBJ>(parts, grid, waves, d, a);
+          case 1: return launch_reg<1, OBJ>(parts, grid, waves, d, a);
+          case 2: return launch_reg<2, OBJ>(parts, grid, waves, d, a);
+          case 3: return launch_reg<3, OBJ>(parts, grid, waves, d, a);
+          case 4: return launch_reg<4, OBJ>(parts, grid, waves, d, a);
+          default: return launch_reg<sa::kRegAny, OBJ>(false, grid, waves, d, a);
         }
       });
     } else {
@@ -530,12 +541,15 @@ struct MultiArgs {
 
 template <int LG, int OBJ>
 hipError_t launch_multi_reg(bool parts, int grid, int waves, int groups, const sa::DevModel &d, const MultiArgs &a) {
-  if (parts)
-    sa::multi_reg_h_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.n, a.instances, a.chains, groups, a.iters,
-                                                                       a.T0, a.alpha, a.k0, a.k1, a.swap_thr, a.srch,
-                                                                       a.w);
-  else
-    sa::multi_reg_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.n, a.instances, a.chains, groups, a.iters,
+  if constexpr (LG >= 0) {
+    if (parts) {
+      sa::multi_reg_h_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.n, a.instances, a.chains, groups, a.iters,
+                                                                         a.T0, a.alpha, a.k0, a.k1, a.swap_thr, a.srch,
+                                                                         a.w);
+      return hipGetLastError();
+    }
+  }
+  sa::multi_reg_kernel<LG, OBJ><<<grid, waves * 64, 0, a.stream>>>(d, a.n, a.instances, a.chains, groups, a.iters,
                                                                      a.T0, a.alpha, a.k0, a.k1, a.swap_thr, a.srch,
                                                                      a.w);
   return hipGetLastError();
@@ -570,25 +584,27 @@ hipError_t launch_multi_cont(size_t lds, const sa::DevModel &d, const MultiArgs 
 // The kernels a sched_anneal_multi may run, in order of preference. Continuous admission: list
 // scheduling by the most requests an instance holds, else the full-replay kernel. Static:
 // the register kernel when every instance holds at most 64 requests, its two- and
-// three-position form when every instance holds at most 192 (batches of 1 .. 16, a power of
-// two, on the 32-bit pair-cost widths); the LDS delta kernels, laid out for the whole queue
+// three-position form when every instance holds at most 192 and batches are a power of two up
+// to 16 (both on the 32-bit pair-cost widths); the LDS delta kernels, laid out for the whole queue
 // (an instance never holds more); always last the full-replay kernel (LDS for the whole
 // queue too).
 template <int OBJ>
 void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const MultiArgs &a) {
   const int B = model->max_batch, n = a.n, total = a.instances * a.chains;
   const int cus = std::max(1, cu_count());
-  if (model->policy == SCHED_STATIC && sa::reg_parts(1, B) > 0) {
+  if (model->policy == SCHED_STATIC &&
+      (sa::reg_form(B) != sa::kRegAny || reg_any_pays((n + a.instances - 1) / a.instances, B))) {
     const int waves = total >= 4 * cus && a.chains >= 4 ? 4 : (total >= 2 * cus && a.chains >= 2 ? 2 : 1);
     const int groups = (a.chains + waves - 1) / waves, grid = a.instances * groups;
-    for (int parts = 0; parts <= 1; ++parts) {
+    for (int parts = 0; parts <= (sa::reg_form(B) == sa::kRegAny ? 0 : 1); ++parts) {
       c.add(kSN | (parts ? sa::kFlagInst192 : sa::kFlagInst64), kMultiFlags | kT32, [=](const sa::DevModel &d) {
-        switch (B) {
-          case 1: return launch_multi_reg<0, OBJ>(parts, grid, waves, groups, d, a);
-          case 2: return launch_multi_reg<1, OBJ>(parts, grid, waves, groups, d, a);
-          case 4: return launch_multi_reg<2, OBJ>(parts, grid, waves, groups, d, a);
-          case 8: return launch_multi_reg<3, OBJ>(parts, grid, waves, groups, d, a);
-          default: return launch_multi_reg<4, OBJ>(parts, grid, waves, groups, d, a);
+        switch (sa::reg_form(B)) {
+          case 0: return launch_multi_reg<0, OBJ>(parts, grid, waves, groups, d, a);
+          case 1: return launch_multi_reg<1, OBJ>(parts, grid, waves, groups, d, a);
+          case 2: return launch_multi_reg<2, OBJ>(parts, grid, waves, groups, d, a);
+          case 3: return launch_multi_reg<3, OBJ>(parts, grid, waves, groups, d, a);
+          case 4: return launch_multi_reg<4, OBJ>(parts, grid, waves, groups, d, a);
+          default: return launch_multi_reg<sa::kRegAny, OBJ>(false, grid, waves, groups, d, a);
         }
       });
     }

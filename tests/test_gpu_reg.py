@@ -289,3 +289,22 @@ def _reg_fit_sweep_case(sl, orc, rng, n, B, policy, scale, seed):
         assert rec[c].tolist() == w["rec"].tolist(), c
         assert cur[c].tolist() == w["cur"].tolist() and best[c].tolist() == w["best"].tolist(), c
         assert cs[c].tolist() == w["cur_starts"].tolist() and bs[c].tolist() == w["best_starts"].tolist(), c
+
+
+# batches of any size up to 32 in the register kernel: one or two rounds of member gathers, a
+# ragged last batch, a last batch of one, batches that straddle the 16-lane rows
+ANY_BATCH = [(4, 3), (31, 3), (64, 3), (64, 5), (41, 8 + 1), (13, 12), (64, 15), (50, 17), (63, 31), (64, 32), (33, 32)]
+
+
+@pytest.mark.parametrize("n,B", ANY_BATCH)
+@pytest.mark.parametrize("thr,search,wide", [(1 << 31, None, False), (0, (1, 6, 1), False), (1 << 32, None, True)])
+def test_reg_kernel_any_batch(sl, orc, n, B, thr, search, wide):
+    rng = np.random.default_rng(n * 131 + B * 7 + (thr >> 30))
+    if wide:  # timelines beyond 32 bits
+        q = random_queue(rng, n, max_in=3000, max_out=250, thr_hi=4_000_000_000)
+        m = Model(B, 0, p0=5_000_000, p1=100, d0=8_000_000, d1=1000, d2=3, swap_threshold=thr)
+    else:
+        q = random_queue(rng, n, max_in=3000, max_out=150, thr_hi=60_000 * n)
+        m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2, swap_threshold=thr)
+    assert _static_narrow(q, m)
+    _run_check(sl, orc, q, m, 5, 300, 0.8, 0.99, 3, search)
