@@ -218,6 +218,17 @@ size_t anneal_lds_bytes(int n) {
   return ((size_t)n * 16 + 15) / 16 * 16 + per_wave * sa::kWavesPerBlock;
 }
 
+// Chains per workgroup of the kernels with one LDS block per chain behind shared records: at
+// most 16 and what the LDS holds, and no more than spread the chains evenly over the CUs in as
+// many passes as that takes (1500 chains: 250 workgroups of 6; in 188 workgroups of 8 a quarter
+// of the CUs idled). 0 when not even one chain fits.
+int lds_waves(int chains, size_t shared, size_t per, int lim, int cus) {
+  if (shared + per > (size_t)lim) return 0;
+  const int64_t fit = std::min<int64_t>(16, ((int64_t)lim - (int64_t)shared) / (int64_t)per);
+  const int64_t passes = (chains + fit * cus - 1) / (fit * cus);
+  return (int)((chains + passes * cus - 1) / (passes * cus));
+}
+
 // Whether the register kernel's form for any batch size beats the LDS delta kernels: its cost
 // grows with the batch (two lane gathers per member: 64 requests in batches of 3 take 2.6 ms
 // against 6.0 ms, of 24 1.27 against 1.94 ms, of 33 1.31 against 1.27 ms), and when one batch
@@ -278,10 +289,8 @@ void add_sized(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, c
   } else {
     const size_t soa = (size_t)(n + 1) * 16, per = sized_chain_lds(n);
     const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
-    int waves = 1;
-    while (waves < 16 && (int64_t)waves * cus < a.chains) waves <<= 1;
-    while (waves > 1 && soa + per * waves > (size_t)lim) waves >>= 1;
-    if (soa + per * waves <= (size_t)lim) {
+    const int waves = lds_waves(a.chains, soa, per, lim, cus);
+    if (waves > 0) {
       const size_t lds = soa + per * waves;
       const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
       const int grid = (a.chains + waves - 1) / waves;
@@ -442,28 +451,23 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
         }
       });
     } else {
-      // chains per workgroup: enough to spread the chains over every CU, at most 16 and at
-      // most what the LDS holds
       int lg = 0;
       while ((1 << lg) < B) ++lg;
       const size_t soa = (size_t)(n + 1) * 16;
       const size_t per = lg == 6 ? wave_chain_lds(n, B) : static_wave_lds(n, B);
       const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
-      int waves = 1;
-      while (waves < 16 && (int64_t)waves * cus < a.chains) waves <<= 1;
-      while (waves > 1 && soa + per * waves > (size_t)lim) waves >>= 1;
-      if (soa + per * waves <= (size_t)lim && (waves >= 4 || (int64_t)waves * cus >= a.chains)) {
+      const int waves = lds_waves(a.chains, soa, per, lim, cus);
+      if (waves >= 4 || (waves > 0 && (int64_t)waves * cus >= a.chains)) {
         const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)B + 1};
         const size_t lds = soa + per * waves;
         if (lg == 6) {
           // the limit-row kernel when the whole timeline fits 32 bits (its chains take a
           // little more LDS: the order carries 64 spare entries)
           const size_t rper = sa::rows_chain_bytes(n, B);
-          int rwaves = waves;
-          while (rwaves > 1 && soa + rper * rwaves > (size_t)lim) rwaves >>= 1;
+          const int rwaves = lds_waves(a.chains, soa, rper, lim, cus);
           const size_t rlds = soa + rper * rwaves;
           const int rows = sa::limit_rows_for((n + B - 1) / B);
-          if (rlds <= (size_t)lim && (rwaves >= 4 || (int64_t)rwaves * cus >= a.chains))
+          if (rwaves >= 4 || (rwaves > 0 && (int64_t)rwaves * cus >= a.chains))
             c.add(kSN | kT32, kAnnealFlags, [=](const sa::DevModel &d) {
               switch (rows) {
                 case 8: return launch_rows<OBJ, 8>(rwaves, rlds, d, sp, a);
@@ -495,11 +499,9 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
                          (ls ? ((sa::cont_ls_scratch_bytes(n) + 15) & ~size_t(15)) : 0) +
                          (inc ? sa::cont_inc_bytes(n, B) : 0);
       const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
-      int waves = 1;
-      while (waves < 16 && (int64_t)waves * cus < a.chains) waves <<= 1;
-      while (waves > 1 && soa + per * waves > (size_t)lim) waves >>= 1;
+      const int waves = lds_waves(a.chains, soa, per, lim, cus);
+      if (waves == 0) continue;
       const size_t lds = soa + per * waves;
-      if (lds > (size_t)lim) continue;
       const int grid = (a.chains + waves - 1) / waves;
       const uint32_t need = sa::kFlagNarrowPrefill | (ls ? sa::kFlagListSched : 0u);
       c.add(need, kAnnealFlags, [=](const sa::DevModel &d) {
