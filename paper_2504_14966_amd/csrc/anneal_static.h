@@ -240,14 +240,11 @@ struct Seg {
         excl = g == 0 ? 0 : (g == 1 ? s[0] : (g == 2 ? s[0] + s[1] : s[0] + s[1] + s[2]));
       }
     } else {
-      int64_t x = (lane & (Bp - 1)) == 0 ? v : 0;
-#pragma unroll
-      for (int o = Bp; o < kWave; o <<= 1) {
-        const int64_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
-      excl = __shfl(x, lane & ~(Bp - 1)) - v;
-      total = __shfl(x, kWave - Bp);
+      // only the leaders contribute, so every lane of a segment holds its leader's sum; DPP
+      // scan (as lane shuffles through the LDS this took 5 to 8 of its round trips per row)
+      const uint64_t x = scan_add64((lane & (Bp - 1)) == 0 ? (uint64_t)v : 0ull);
+      excl = (int64_t)x - v;
+      total = (int64_t)rl64(x, kWave - 1);
     }
   }
   __device__ static __forceinline__ int count(bool p, int seg) {
@@ -268,7 +265,7 @@ struct Seg {
       }
       return s;
     } else {
-      return (int64_t)wave_sum_u64((uint64_t)v);
+      return (int64_t)wave_sum_u64_dpp((uint64_t)v);
     }
   }
 };
