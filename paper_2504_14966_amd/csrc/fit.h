@@ -17,6 +17,7 @@
 // per member one closed form, per batch a wave maximum. All arithmetic is 64-bit.
 #pragma once
 #include "anneal_sized.h"
+#include "anneal_wave.h"
 
 namespace sa {
 
@@ -405,6 +406,240 @@ __global__ void __launch_bounds__(1024) start_fit_kernel(DevFit f, QueuePtrs q, 
       h->best_t = -1;
     }
   }
+}
+
+// ---- chains when every member's time fits 32 bits: windows restarted at the first change ----
+//
+// The replay's windows are whole batches, and any division into windows gives the same totals.
+// So a chain keeps, for every window of its current order, the window's first position, the
+// start time there (saturated) and the totals before it, and a proposal is replayed from the
+// last window that begins at or before the first batch whose members it changes. The candidate
+// is read from the current order through a position map and an edit of at most two start
+// flags, and nothing is copied unless it is accepted.
+
+// Windows kept per order. As formed, two neighbours hold more than 64 positions (33 windows at
+// most); later changes behind a kept window can leave smaller ones, and those past the last
+// entry are not kept.
+constexpr int kFitWindows = 36;
+struct FitWindows {
+  uint32_t first[kFitWindows], start[kFitWindows], met[kFitWindows];
+  uint64_t total[kFitWindows];
+};
+
+// Flags of the candidate: position set0 becomes a start, clr0 stops being one (-1: neither).
+struct FlagEdit {
+  int set0, clr0;
+  __device__ __forceinline__ bool at(const uint8_t *f, int p) const { return (f[p] != 0 && p != clr0) || p == set0; }
+};
+
+// Record for these chains: x = l_in | l_out << 16, y and w the thresholds (the TPOT ones
+// multiplied by l_out, saturated: member times are below 2^32 - 1), z = kind.
+__device__ __forceinline__ void load_fit_requests32(const QueuePtrs &q, const uint32_t *thr2, int n, uint4 *req) {
+  for (int r = threadIdx.x; r < n; r += blockDim.x) {
+    const uint32_t lin = q.in_len[r], L = q.out_len[r], kind = q.kind[r], t1 = q.thr[r], t2 = thr2 ? thr2[r] : 0u;
+    const uint64_t cap = 0xFFFFFFFFull;
+    req[r] = make_uint4(lin | (L << 16), kind == 1 ? (uint32_t)min((uint64_t)t1 * L, cap) : t1, kind,
+                        (uint32_t)min((uint64_t)t2 * L, cap));
+  }
+}
+
+// Replays windows w0, w0 + 1, ... from the state `win` holds for w0 (position, start, totals
+// before it), leaving the state of every later window in `out`; returns the totals of the
+// whole order and the number of windows kept in `count`.
+__device__ __forceinline__ Score replay_fit_from(const DevFit &f, const uint4 *__restrict__ req, const uint16_t *perm,
+                                                 const Remap rm, const uint8_t *flags, const FlagEdit ed,
+                                                 const FitWindows &win, FitWindows &out, int w0, int &count) {
+  const int lane = lane_id();
+  const int n = f.n;
+  const uint32_t ap = (uint32_t)f.ap, bp = (uint32_t)f.bp, cp = (uint32_t)f.cp, dp = (uint32_t)f.dp;
+  const uint32_t ad = (uint32_t)f.ad, bd = (uint32_t)f.bd, cd = (uint32_t)f.cd, dd = (uint32_t)f.dd;
+  int s = uniform((int)win.first[w0]), wi = w0;
+  uint32_t S0 = (uint32_t)uniform((int)win.start[w0]);
+  int64_t nmet = uniform((int)win.met[w0]);
+  uint64_t total = rl64(win.total[w0], 0);
+  for (;;) {
+    const int p = s + lane, pc = min(p, n - 1);
+    const uint4 rq = req[perm[rm.src(pc)]];
+    const bool st = p >= n ? p == n : (lane == 0 || ed.at(flags, p));
+    const bool st64 = s + kWave >= n ? s + kWave == n : ed.at(flags, s + kWave);
+    uint64_t lastm = (__ballot(st) >> 1) | (st64 ? uint64_t(1) << 63 : 0ull);
+    if (lastm == 0ull) lastm = uint64_t(1) << 63;
+    const int w = 64 - __clzll(lastm);
+    const bool in = lane < w;
+    const uint64_t below = lastm & ((uint64_t(1) << lane) - 1);
+    const int b0 = below ? 64 - __clzll(below) : 0;
+    const int b1 = lane + __builtin_ctzll(in ? (lastm >> lane) : 1ull);
+    const uint32_t b = (uint32_t)(b1 - b0 + 1), l = rq.x & 0xFFFFu, L = rq.x >> 16, kind = rq.z;
+    const uint32_t tp = ap * b * l + bp * b + cp * l + dp;
+    const uint32_t td = L * (bd * b + dd) + (ad * b + cd) * (L * l + ((L * (L + 1u)) >> 1));
+    const uint32_t E = in ? tp + td : 0u;
+    // lanes past the window hold E = 0 and send nothing; what they receive is unused
+    const uint32_t D = seg_max32(E, b0, b1, lane);
+    const bool last = in && lane == b1;
+    const uint32_t contrib = last ? D : 0u;
+    const uint32_t excl =
+        scan_add_sat32((uint32_t)__builtin_amdgcn_update_dpp(0, (int)contrib, kDppWaveShr1, 0xF, 0xF, false));
+    const uint32_t S = add_sat(S0, excl), ttft = add_sat(S, tp), e2e = add_sat(S, E);
+    const bool met = in && (kind == 0 ? ttft <= rq.y
+                                      : (kind == 1 ? td <= rq.y : (kind == 2 ? e2e <= rq.y : ttft <= rq.y && td <= rq.w)));
+    nmet += __popcll(__ballot(met));
+    // member times plus each batch's duration times the requests after it, in 16-bit halves:
+    // a sum is at most 64 (2^16 - 1) (1 + 1023) < 2^32
+    const uint32_t after = last ? (uint32_t)(n - 1 - p) : 0u;
+    uint32_t lo = (E & 0xFFFFu) + (contrib & 0xFFFFu) * after, hi = (E >> 16) + (contrib >> 16) * after;
+    wave_all2<OpAdd, OpAdd>(lo, hi);
+    total += (uint64_t)lo + ((uint64_t)hi << 16);
+    s += w;
+    if (s >= n) break;
+    S0 = add_sat(S0, add_sat(readlane(excl, kWave - 1), readlane(contrib, kWave - 1)));
+    if (wi + 1 < kFitWindows) {
+      ++wi;
+      if (lane == 0) {
+        out.first[wi] = (uint32_t)s;
+        out.start[wi] = S0;
+        out.met[wi] = (uint32_t)nmet;
+        out.total[wi] = total;
+      }
+    }
+  }
+  count = wi + 1;
+  return Score{nmet, total};
+}
+
+__host__ __device__ __forceinline__ size_t fit_chain_bytes(int n) {
+  return (((size_t)n * 2 + 15) & ~size_t(15)) + (((size_t)n + 15) & ~size_t(15)) + 2 * sizeof(FitWindows);
+}
+static_assert(sizeof(FitWindows) % 16 == 0, "two of them follow each other in the LDS");
+
+// One wave per chain. Fixed-size batches take swap / insert proposals (swap iff w0 < swap_thr);
+// the batch-size search takes squeeze / delay / swap. Per-wave LDS: the current order and
+// flags, the windows of the current order and of the candidate. Bound by the waves' latency:
+// per window one dependent chain of two LDS reads, the closed forms, a max-scan, an add-scan
+// and a reduction (reading the next window's records beside it made the 256-request chains
+// 7 % slower). 256 requests, batches up to 16 searched, 2048 chains x 2000: 5.1 ms, with full
+// replays of copied candidates 6.5 ms.
+template <int OBJ>
+__global__ void __launch_bounds__(1024) anneal_fit_windows_kernel(DevFit f, QueuePtrs q, const uint32_t *thr2,
+                                                                  int chains, int iters, double T0, double alpha,
+                                                                  uint32_t key0, uint32_t key1, uint64_t swap_thr,
+                                                                  SearchParams srch, unsigned char *ws) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  if (!fit_gate_open(ws, f)) return;
+  const int n = f.n, B = f.B;
+  const bool search = f.policy == 2;
+  uint4 *req = reinterpret_cast<uint4 *>(lds);
+  const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
+  const int wave = uniform((int)(threadIdx.x >> 6));
+  unsigned char *wb = lds + (size_t)n * 16 + (size_t)wave * fit_chain_bytes(n);
+  uint16_t *cur = reinterpret_cast<uint16_t *>(wb);
+  uint8_t *fcur = wb + pb;
+  FitWindows &win = *reinterpret_cast<FitWindows *>(wb + pb + fb), &cand = *(&win + 1);
+  load_fit_requests32(q, thr2, n, req);
+  __syncthreads();
+  const int chain = uniform((int)blockIdx.x * (int)(blockDim.x >> 6) + wave);
+  if (chain >= chains) return;
+  const int lane = lane_id();
+  const WsHeader *h = reinterpret_cast<const WsHeader *>(ws);
+  const int64_t t_ref = h->t_ref, allmet = h->allmet;
+  const uint16_t *start = reinterpret_cast<const uint16_t *>(ws + ws_off_start());
+  const size_t stride = ws_perm_stride(n), fstride = ws_flag_stride(n);
+  uint16_t *gbest = reinterpret_cast<uint16_t *>(ws + ws_off_best(n, chains)) + (size_t)chain * stride;
+  uint16_t *gcur = reinterpret_cast<uint16_t *>(ws + ws_off_cur(n, chains)) + (size_t)chain * stride;
+  uint8_t *gbest_f = ws + ws_off_best_starts(n, chains) + (size_t)chain * fstride;
+  uint8_t *gcur_f = ws + ws_off_cur_starts(n, chains) + (size_t)chain * fstride;
+  for (int p = lane; p < n; p += kWave) {
+    const uint16_t v = start[p];
+    const uint8_t fl = (uint8_t)(p % B == 0);
+    cur[p] = v;
+    fcur[p] = fl;
+    gbest[p] = v;
+    gbest_f[p] = fl;
+  }
+  if (lane == 0) {
+    win.first[0] = 0u;
+    win.start[0] = 0u;
+    win.met[0] = 0u;
+    win.total[0] = 0ull;
+  }
+  wave_sync_lds();
+  int count;  // windows of the current order
+  const Score s0 = replay_fit_from(f, req, cur, Remap{0, 0, 0}, fcur, FlagEdit{-1, -1}, win, win, 0, count);
+  wave_sync_lds();
+  int64_t cn = s0.n;
+  uint64_t ct = s0.t;
+  int64_t bn = cn, biter = -1, accepts = 0;
+  uint64_t bt = ct, digest = kFnvOffset;
+  Cooling cool{T0, alpha, srch.level_len, srch.level_len};
+  SizedDraws ds;
+  ProposalStream ps;
+  const int iters_run = (srch.early_exit && allmet) ? 0 : iters;
+  for (int k = 0; k < iters_run; ++k) {
+    uint32_t w3;
+    SizedMove mv;
+    if (search) {
+      if ((k & (kWave - 1)) == 0) ds.refill(k, lane, n, (uint32_t)chain, key0, key1);
+      const uint32_t pk = ds.packed(k);
+      w3 = ds.word3(k);
+      mv = plan_move(fcur, n, B, (int)(pk >> 20), (int)(pk & 1023u), (int)((pk >> 10) & 1023u), lane);
+    } else {
+      if ((k & (kWave - 1)) == 0) ps.refill(k, lane, n, (uint32_t)chain, key0, key1, swap_thr, 0);
+      const uint32_t pk = ps.packed(k);
+      w3 = ps.word3(k);
+      const int i = (int)(pk & 1023u), j = (int)((pk >> 10) & 1023u);
+      // a fixed-size move: swap (op 2) or insert (op 3: from i to j, flags untouched)
+      mv = SizedMove{true, ((pk >> 20) & 1u) ? 3 : 2, i, j, j, -1, -1};
+    }
+    if (mv.made) {
+      const Remap rm = mv.op == 2 ? Remap{1, mv.i, mv.j} : Remap{2, mv.i, mv.op == 3 ? mv.j : mv.to};
+      const FlagEdit ed{mv.set0, mv.clr0};
+      // the first position whose member or batch changes: a move's lower end; squeeze and delay
+      // also change the size of the batch before or around it
+      int lo = min(rm.i, rm.j);
+      if (mv.op == 0)
+        lo = mv.to - 1;  // the batch the request joins ends there
+      const bool begins = lane < count && (int)win.first[min(lane, kFitWindows - 1)] <= lo;
+      const int w0 = __popcll(__ballot(begins)) - 1;
+      // a fixed-size move inside one batch changes nothing but the order
+      const bool same = !search && mv.i / B == mv.j / B;
+      int nc = count;
+      const Score s = same ? Score{cn, ct} : replay_fit_from(f, req, cur, rm, fcur, ed, win, cand, w0, nc);
+      if (obj_accept<OBJ>(cn, ct, s.n - cn, (int64_t)(s.t - ct), t_ref, cool.T, w3)) {
+        wave_sync_lds();
+        if (!same && lane > w0 && lane < nc) {
+          win.first[lane] = cand.first[lane];
+          win.start[lane] = cand.start[lane];
+          win.met[lane] = cand.met[lane];
+          win.total[lane] = cand.total[lane];
+        }
+        count = nc;
+        if (mv.op == 3)
+          apply_move_lds(cur, 2, mv.i, mv.j, lane);
+        else
+          apply_sized_move(cur, fcur, mv, lane);
+        cn = s.n;
+        ct = s.t;
+        ++accepts;
+        digest = (digest ^ (uint64_t)k) * kFnvPrime;
+        digest = (digest ^ (uint64_t)cn) * kFnvPrime;
+        digest = (digest ^ ct) * kFnvPrime;
+        if (obj_better<OBJ>(cn, ct, bn, bt)) {
+          bn = cn;
+          bt = ct;
+          biter = k;
+          for (int p = lane; p < n; p += kWave) {
+            gbest[p] = cur[p];
+            gbest_f[p] = fcur[p];
+          }
+        }
+      }
+    }
+    cool.step();
+  }
+  for (int p = lane; p < n; p += kWave) {
+    gcur[p] = cur[p];
+    gcur_f[p] = fcur[p];
+  }
+  if (lane == 0) write_record(ws, n, chain, cn, ct, bn, bt, biter, accepts, digest, allmet);
 }
 
 // One wave per chain, four per workgroup; full replay per proposal. Fixed-size batches take

@@ -1085,6 +1085,27 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
       return hipGetLastError();
     });
   }
+  {
+    // member times in 32 bits: windows restarted at the first change
+    const size_t soa = (size_t)n * 16, per = sa::fit_chain_bytes(n);
+    const int waves = lds_waves(chains, soa, per, max_lds_per_block(), std::max(1, cu_count()));
+    if (waves > 0) {
+      const size_t lds = soa + per * waves;
+      const int grid = (chains + waves - 1) / waves;
+      c.add(sa::kFlagFitMember32, kFitFlags, [=](const sa::DevFit &d) {
+        auto go = [&](auto kernel) {
+          if (lds > 65536) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+          }
+          kernel<<<grid, waves * 64, lds, stream>>>(d, qp, tpot_thr, chains, iters, T0, alpha, k0, k1, st, srch, w);
+          return hipGetLastError();
+        };
+        return srch.objective ? go(&sa::anneal_fit_windows_kernel<1>) : go(&sa::anneal_fit_windows_kernel<0>);
+      });
+    }
+  }
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (2 * pb + 2 * fb);
   const int grid = (chains + 3) / 4;

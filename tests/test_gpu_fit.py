@@ -191,3 +191,27 @@ def test_fit_huge_times_batch_replay(sl, orc, policy):
     for c in range(4):
         w = orc.anneal_chain_fit(q, fo, c, 50, 0.5, 0.99, 3, start_info=info)
         assert res["rec"][c].tolist() == w["rec"].tolist(), c
+
+
+@pytest.mark.parametrize("n,B,policy,search", [(65, 1, 2, None), (65, 64, 2, (1, 9, 0)), (129, 64, 0, None),
+                                               (130, 63, 2, None), (257, 17, 2, (1, 30, 1)), (400, 3, 0, (0, 5, 0)),
+                                               (400, 3, 2, None), (1000, 40, 2, None), (1024, 1, 0, None)])
+def test_anneal_fit_restarted_windows(sl, orc, n, B, policy, search):
+    # member times in 32 bits at every batch size: replays restarted at the window of the first
+    # change, over enough proposals that searched layouts leave windows of many sizes; windows
+    # of one batch, of 64 batches, batches of 64
+    rng = np.random.default_rng(n + 3 * B + policy)
+    q = random_queue(rng, n, max_in=2000, max_out=100, thr_hi=40_000_000)
+    q.kind[::4] = 3
+    thr2 = rng.integers(20_000, 60_000, n).astype(np.uint32)
+    coef = dict(ap=3, bp=500, cp=20, dp=4000, ad=1, bd=70, cd=5, dd=9000)
+    fd, fo = sl.FitModel(B, policy, **coef), orc.FitModel(B, policy, **coef)
+    chains, iters = 3, 1500 if n < 300 else 400
+    res = _anneal(sl, q, fd, chains, iters, 1.0, 0.99, 3, thr2, search)
+    s_orc = orc.Search(*search) if search else None
+    info = orc.start_fit(q, fo, s_orc, thr2)
+    for c in range(chains):
+        w = orc.anneal_chain_fit(q, fo, c, iters, 1.0, 0.99, 3, search=s_orc, thr2=thr2, start_info=info)
+        assert res["rec"][c].tolist() == w["rec"].tolist(), c
+        assert res["cur"][c].tolist() == w["cur"].tolist() and res["best"][c].tolist() == w["best"].tolist(), c
+        assert res["cs"][c].tolist() == w["cur_starts"].tolist() and res["bs"][c].tolist() == w["best_starts"].tolist(), c
