@@ -24,6 +24,7 @@
 #include "anneal_cont_spec.h"
 #include "multi.h"
 #include "anneal_reg.h"
+#include "anneal_row16.h"
 #include "fit.h"
 
 namespace {
@@ -329,6 +330,16 @@ hipError_t launch_reg(bool parts, int grid, int waves, const sa::DevModel &d, co
   return hipGetLastError();
 }
 
+// Whether a run stays so hot that most proposals are kept: the temperature of its last proposal
+// is at least 4, where a candidate that loses one of the met requests (an energy gap of about 1)
+// is still kept with probability 0.78. The paper's schedule ends at 20. (One of 8 or more chains
+// of 10 requests cooled from 1 to 0.01 keeps 59 %: with four proposals per round it took
+// 1.2 ms per 2000 proposals where the register kernel takes 1.0 ms.)
+bool stays_hot(const ChainArgs &a) {
+  const double levels = a.iters > 0 ? (double)((a.iters - 1) / a.srch.level_len) : 0.0;
+  return a.T0 >= 4.0 && a.T0 * std::pow(a.alpha, levels) >= 4.0;
+}
+
 template <int OBJ, int MR>
 hipError_t launch_rows(int waves, size_t lds, const sa::DevModel &d, const sa::StaticParams &sp, const ChainArgs &a) {
   if (lds > 65536) {
@@ -437,6 +448,24 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
     return;
   }
   if (model->policy == SCHED_STATIC) {
+    if (n <= 16 && n > B && stays_hot(a)) {
+      // 32-bit timelines: four proposals per round
+      const int waves = reg_waves(a.chains), grid = (a.chains + waves - 1) / waves;
+      c.add(kSN | kT32, kAnnealFlags, [=](const sa::DevModel &d) {
+        auto go = [&](auto kernel) {
+          kernel<<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0, a.k1, a.swap_thr,
+                                                    a.srch, a.w);
+          return hipGetLastError();
+        };
+        switch (sa::reg_form(B)) {
+          case 0: return go(&sa::anneal_row16_kernel<0, OBJ>);
+          case 1: return go(&sa::anneal_row16_kernel<1, OBJ>);
+          case 2: return go(&sa::anneal_row16_kernel<2, OBJ>);
+          case 3: return go(&sa::anneal_row16_kernel<3, OBJ>);
+          default: return go(&sa::anneal_row16_kernel<sa::kRegAny, OBJ>);
+        }
+      });
+    }
     if ((n <= 64 && (sa::reg_form(B) != sa::kRegAny || reg_any_pays(n, B))) || sa::reg_parts(n, B) > 1) {
       const bool parts = n > 64;
       const int waves = reg_waves(a.chains), grid = (a.chains + waves - 1) / waves;

@@ -308,3 +308,21 @@ def test_reg_kernel_any_batch(sl, orc, n, B, thr, search, wide):
         m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2, swap_threshold=thr)
     assert _static_narrow(q, m)
     _run_check(sl, orc, q, m, 5, 300, 0.8, 0.99, 3, search)
+
+
+# hot chains of at most 16 requests (four proposals per round): every batch form, a ragged last
+# batch, both moves and objectives, temperatures per proposal and per level (levels that end
+# inside a round), proposal counts that end inside one, and thresholds that make some proposals lose
+@pytest.mark.parametrize("n,B", [(2, 1), (16, 1), (9, 2), (16, 2), (10, 4), (16, 8), (13, 8), (11, 3), (16, 5), (15, 11),
+                                 (16, 15), (7, 6)])
+@pytest.mark.parametrize("thr,search,iters,T0", [(1 << 31, None, 301, 8.0), (0, (1, 3, 0), 130, 500.0),
+                                                 (1 << 32, (0, 5, 1), 255, 6.0), (1 << 31, (1, 100, 0), 402, 5.0)])
+def test_hot_rows(sl, orc, n, B, thr, search, iters, T0):
+    rng = np.random.default_rng(n * 131 + B * 7 + iters)
+    q = random_queue(rng, n, max_in=3000, max_out=150, thr_hi=60_000 * n)
+    m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2, swap_threshold=thr)
+    assert _static_narrow(q, m) and _timeline_end(q, m) < 2**32 - 2
+    _run_check(sl, orc, q, m, 6, iters, T0, 0.9995, 17, search)
+    # the same with wide energy gaps, so that proposals are rejected
+    m.t_ref_us = 2000
+    _run_check(sl, orc, q, m, 6, iters, T0, 0.9995, 18, search)
