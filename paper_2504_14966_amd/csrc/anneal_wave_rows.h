@@ -1,5 +1,6 @@
-// Annealing chains under static admission, one batch per wave (33 <= B <= 64), with the SLO
-// limit of every member held in registers; for queues whose whole timeline fits 32 bits.
+// Annealing chains under static admission, one batch per wave (17 <= B <= 64, at most 32
+// batches), with the SLO limit of every member held in registers; for queues whose whole
+// timeline fits 32 bits.
 //
 // The delta re-simulation is that of the one-batch-per-wave kernel: a move changes the
 // members of batches a..c by one leaving request o and one joining request e each, and the

@@ -257,8 +257,7 @@ struct ChainArgs {
 };
 
 static_assert(sa::sized_rows_for(SCHED_MAX_N) * 64 >= SCHED_MAX_N, "register rows must cover every position");
-static_assert(sa::limit_rows_for((SCHED_MAX_N + 32) / 33) * 33 >= SCHED_MAX_N,
-              "limit rows must cover every batch when batches hold 33 or more");
+static_assert(sa::limit_rows_for(32) >= 32, "limit rows must cover every batch of a queue that takes them");
 
 template <int OBJ, int NR>
 hipError_t launch_sized(int grid, int waves, size_t lds, const sa::DevModel &d, const sa::StaticParams &sp,
@@ -339,6 +338,15 @@ bool stays_hot(const ChainArgs &a) {
   const double levels = a.iters > 0 ? (double)((a.iters - 1) / a.srch.level_len) : 0.0;
   return a.T0 >= 4.0 && a.T0 * std::pow(a.alpha, levels) >= 4.0;
 }
+
+// One batch per wave with limit rows (timelines of 32 bits): batches of 17 and more, at most 32
+// of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
+// other kernel's rows of two batches cost it more than twice a limit row (bounds, recounts):
+// 1500 chains of 389 requests in batches of 24 took 4.9 ms per 1000 proposals on it and 4.1 ms
+// here; batches of 17: 3.4 against 2.8; 32: 3.2 against 2.4 (1024 chains of 256 requests) and 3.2
+// against 2.8 (4096 of 1000). With four batches in one of its rows it wins: 500 requests in
+// batches of 16: 2.2 against 2.9, in batches of 8 1.9 against 2.8.
+bool rows_pay(int n, int B) { return B >= 17 && (n + B - 1) / B <= 32; }
 
 template <int OBJ, int MR>
 hipError_t launch_rows(int waves, size_t lds, const sa::DevModel &d, const sa::StaticParams &sp, const ChainArgs &a) {
@@ -489,7 +497,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
       if (waves >= 4 || (waves > 0 && (int64_t)waves * cus >= a.chains)) {
         const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)B + 1};
         const size_t lds = soa + per * waves;
-        if (lg == 6) {
+        if (rows_pay(n, B)) {
           // the limit-row kernel when the whole timeline fits 32 bits (its chains take a
           // little more LDS: the order carries 64 spare entries)
           const size_t rper = sa::rows_chain_bytes(n, B);

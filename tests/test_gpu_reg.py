@@ -326,3 +326,16 @@ def test_hot_rows(sl, orc, n, B, thr, search, iters, T0):
     # the same with wide energy gaps, so that proposals are rejected
     m.t_ref_us = 2000
     _run_check(sl, orc, q, m, 6, iters, T0, 0.9995, 18, search)
+
+
+# the limit-row kernel below 33 per batch: the shortest batches it takes, ragged last batches of one
+# and of all but one, 32 batches (and 33, which it does not take), one batch holding everything
+@pytest.mark.parametrize("n,B", [(65, 17), (103, 17), (543, 17), (544, 17), (545, 17), (389, 24), (97, 32), (95, 32),
+                                 (1024, 32), (20, 20), (30, 32), (200, 31)])
+@pytest.mark.parametrize("thr,search", [(1 << 31, None), (0, None), (1 << 32, (1, 7, 0))])
+def test_limit_rows_short_batches(sl, orc, n, B, thr, search):
+    rng = np.random.default_rng(n * 17 + B)
+    q = random_queue(rng, n, max_in=1500, max_out=100, thr_hi=40_000 * n)
+    m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2, swap_threshold=thr)
+    assert _static_narrow(q, m) and _timeline_end(q, m) < 2**32 - 2
+    _run_check(sl, orc, q, m, 5, 150, 0.7, 0.99, 29, search)
