@@ -331,7 +331,9 @@ def test_hot_rows(sl, orc, n, B, thr, search, iters, T0):
 # the limit-row kernel below 33 per batch: the shortest batches it takes, ragged last batches of one
 # and of all but one, 32 batches (and 33, which it does not take), one batch holding everything
 @pytest.mark.parametrize("n,B", [(65, 17), (103, 17), (543, 17), (544, 17), (545, 17), (389, 24), (97, 32), (95, 32),
-                                 (1024, 32), (20, 20), (30, 32), (200, 31)])
+                                 (1024, 32), (20, 20), (30, 32), (200, 31),
+                                 # 20, 21, 24, 25, 28 and 29 batches: the edges of the rows left out
+                                 (340, 17), (341, 17), (408, 17), (409, 17), (476, 17), (477, 17)])
 @pytest.mark.parametrize("thr,search", [(1 << 31, None), (0, None), (1 << 32, (1, 7, 0))])
 def test_limit_rows_short_batches(sl, orc, n, B, thr, search):
     rng = np.random.default_rng(n * 17 + B)
