@@ -197,14 +197,29 @@ int device_attr(hipDeviceAttribute_t attr, int fallback) {
 int max_lds_per_block() { return device_attr(hipDeviceAttributeMaxSharedMemoryPerBlock, 65536); }
 int cu_count() { return device_attr(hipDeviceAttributeMultiprocessorCount, 256); }
 
+// Both for the current device, asked for once per evaluation call: a small one is bound by the
+// host's launch, and asking up to seven times took 16 continuous rows of 24 requests 10.1 us
+// where this takes 9.5 us.
+struct Limits {
+  int lds = 65536, cus = 256;
+};
+Limits device_limits() {
+  Limits l;
+  int dev = 0, v = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return l;
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) l.lds = v;
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) l.cus = std::max(1, v);
+  return l;
+}
+
 // Workgroups of an evaluation launch. Each forms the verdict and stages the requests first,
 // about 3 us: at 32768 rows of 10 requests, 8192 workgroups took 56 us and 2048 (what the GPU
 // holds at once) 25 us. Beyond that as many as leave every wave four rows, at most 8192: with
 // 2^20 rows of 128 requests, 2048 workgroups end unevenly (eval_static_kernel 678 us against
 // 551 us), and at 131072 rows of 400 requests 2048 take 376 us, 8192 take 332 us.
-int eval_grid(int64_t rows, int waves, size_t lds, int lim, int cus) {
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / waves, (int64_t)lim / (int64_t)(lds + sa::kCheckLdsBytes)));
-  const int64_t most = std::max<int64_t>(per_cu * cus, std::min<int64_t>(8192, rows / (4 * waves)));
+int eval_grid(int64_t rows, int waves, size_t lds, const Limits &dl) {
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / waves, (int64_t)dl.lds / (int64_t)(lds + sa::kCheckLdsBytes)));
+  const int64_t most = std::max<int64_t>(per_cu * dl.cus, std::min<int64_t>(8192, rows / (4 * waves)));
   return (int)std::min<int64_t>((rows + waves - 1) / waves, most);
 }
 
@@ -343,7 +358,7 @@ bool stays_hot(const ChainArgs &a) {
 // of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
 // other kernel's rows of two batches cost it more than twice a limit row (bounds, recounts):
 // 1500 chains of 389 requests in batches of 24 took 4.9 ms per 1000 proposals on it and 4.1 ms
-// here; batches of 17: 3.4 against 2.8; 32: 3.2 against 2.4 (1024 chains of 256 requests) and 3.2
+// here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2 against 2.4 (1024 chains of 256 requests) and 3.2
 // against 2.8 (4096 of 1000). With four batches in one of its rows it wins: 500 requests in
 // batches of 16: 2.2 against 2.9, in batches of 8 1.9 against 2.8.
 bool rows_pay(int n, int B) { return B >= 17 && (n + B - 1) / B <= 32; }
@@ -707,8 +722,9 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
 // short enough queues for the LDS to hold four waves per CU.
 template <bool LAYOUT>
 void add_eval_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
-                    const uint16_t *perms, const uint8_t *starts, int64_t k, int64_t *out, hipStream_t stream) {
-  const int cus = std::max(1, cu_count()), lim = max_lds_per_block() - (int)sa::kCheckLdsBytes;
+                    const uint16_t *perms, const uint8_t *starts, int64_t k, int64_t *out, const Limits &dl,
+                    hipStream_t stream) {
+  const int cus = dl.cus, lim = dl.lds - (int)sa::kCheckLdsBytes;
   if (n < 2 || k < eval_lane_rows(n, model->max_batch, LAYOUT)) return;
   // the tile's ids and flags are read 16 bytes at a time (a tile of 64 rows keeps the alignment)
   if ((reinterpret_cast<uintptr_t>(perms) | reinterpret_cast<uintptr_t>(starts)) & 15u) return;
@@ -733,8 +749,8 @@ void add_eval_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int
 // Continuous evaluation with one order per lane (the list holds the running requests in 8, 16,
 // 32 or 64 registers), for enough rows to give every SIMD a wave.
 void add_eval_cont_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
-                         const uint16_t *perms, int64_t k, int64_t *out, hipStream_t stream) {
-  const int cus = std::max(1, cu_count()), lim = max_lds_per_block() - (int)sa::kCheckLdsBytes;
+                         const uint16_t *perms, int64_t k, int64_t *out, const Limits &dl, hipStream_t stream) {
+  const int cus = dl.cus, lim = dl.lds - (int)sa::kCheckLdsBytes;
   if (k < eval_cont_lane_rows(n)) return;
   const int n0 = std::min(model->max_batch, n), cap = n0 <= 8 ? 8 : (n0 <= 16 ? 16 : (n0 <= 32 ? 32 : 64));
   const size_t shared = (size_t)n * 16, per = sa::cont_lane_wave_bytes(n, cap);
@@ -807,6 +823,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
   const int n = queue->n;
   const sa::DevModel dm = dev_model(model, n);
   const sa::QueuePtrs qp = dev_queue(queue);
+  const Limits dl = device_limits();
   Candidates<sa::DevModel> c;
   if (model->policy != SCHED_CONTINUOUS) {
     // static batches on the 32-bit pair-cost widths: one order per wave with the delta
@@ -815,8 +832,8 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
     while ((1 << lg) < model->max_batch) ++lg;
     const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
     const size_t lds = (size_t)(n + 1) * 16 + ((((size_t)n * 2 + 15) & ~size_t(15)) + 64 * 8 + 32 * 4) * 4;
-    const int g4 = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
-    if (!detail) add_eval_lanes<false>(c, model, n, qp, perms, nullptr, k, out, stream);
+    const int g4 = eval_grid(k, 4, lds, dl);
+    if (!detail) add_eval_lanes<false>(c, model, n, qp, perms, nullptr, k, out, dl, stream);
     c.add(kSN, kEvalFlags | kT32, [=](const sa::DevModel &d) {
 #define SA_EVAL_CASE(L)                                                                            \
   case L:                                                                                          \
@@ -842,12 +859,12 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
   // any widths: one order per wave, up to four waves per workgroup as the LDS allows (with
   // room for list scheduling under continuous admission)
   const bool ls = model->policy == SCHED_CONTINUOUS;
-  if (ls && !detail) add_eval_cont_lanes(c, model, n, qp, perms, k, out, stream);
-  const size_t lim = (size_t)max_lds_per_block() - sa::kCheckLdsBytes;  // the checks' own LDS on top
+  if (ls && !detail) add_eval_cont_lanes(c, model, n, qp, perms, k, out, dl, stream);
+  const size_t lim = (size_t)dl.lds - sa::kCheckLdsBytes;  // the checks' own LDS on top
   int waves = sa::kWavesPerBlock;
   while (waves > 1 && eval_lds_bytes(n, ls, waves) > lim) waves >>= 1;
   const size_t lds = eval_lds_bytes(n, ls, waves);
-  const int grid = eval_grid(k, waves, lds, max_lds_per_block(), cu_count());
+  const int grid = eval_grid(k, waves, lds, dl);
   c.add(0u, kEvalFlags, [=](const sa::DevModel &d) {
     const void *fn = detail ? (const void *)&sa::eval_kernel<true> : (const void *)&sa::eval_kernel<false>;
     if (lds > 65536) {
@@ -963,9 +980,10 @@ int sched_eval_batches(const sched_queue_t *queue, const sched_model_t *model, c
   const int n = queue->n;
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * sa::sized_row_bytes(n);
-  const int grid = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
+  const Limits dl = device_limits();
+  const int grid = eval_grid(k, 4, lds, dl);
   Candidates<sa::DevModel> c;
-  if (!detail) add_eval_lanes<true>(c, model, n, qp, perms, starts, k, out, stream);
+  if (!detail) add_eval_lanes<true>(c, model, n, qp, perms, starts, k, out, dl, stream);
   // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
   // where they hold
   c.add(0u, sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {
@@ -1076,7 +1094,7 @@ int sched_eval_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, con
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (pb + fb + 32 * 4);
-  const int grid = eval_grid(k, 4, lds, max_lds_per_block(), cu_count());
+  const int grid = eval_grid(k, 4, lds, device_limits());
   Candidates<sa::DevFit> c;
   c.add(0u, sa::kFlagFitWindows, [=](const sa::DevFit &d) {
     if (detail)
