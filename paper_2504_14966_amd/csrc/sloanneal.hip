@@ -15,6 +15,7 @@
 
 #include "../../include/sloanneal.h"
 #include "kernels.h"
+#include "launch_shape.h"
 #include "anneal_static.h"
 #include "anneal_wave.h"
 #include "anneal_sized.h"
@@ -234,17 +235,6 @@ size_t anneal_lds_bytes(int n) {
   return ((size_t)n * 16 + 15) / 16 * 16 + per_wave * sa::kWavesPerBlock;
 }
 
-// Chains per workgroup of the kernels with one LDS block per chain behind shared records: at
-// most 16 and what the LDS holds, and no more than spread the chains evenly over the CUs in as
-// many passes as that takes (1500 chains: 250 workgroups of 6; in 188 workgroups of 8 a quarter
-// of the CUs idled). 0 when not even one chain fits.
-int lds_waves(int chains, size_t shared, size_t per, int lim, int cus) {
-  if (shared + per > (size_t)lim) return 0;
-  const int64_t fit = std::min<int64_t>(16, ((int64_t)lim - (int64_t)shared) / (int64_t)per);
-  const int64_t passes = (chains + fit * cus - 1) / (fit * cus);
-  return (int)((chains + passes * cus - 1) / (passes * cus));
-}
-
 // Whether the register kernel's form for any batch size beats the LDS delta kernels: its cost
 // grows with the batch (two lane gathers per member: 64 requests in batches of 3 take 2.6 ms
 // against 6.0 ms, of 24 1.27 against 1.94 ms, of 33 1.31 against 1.27 ms), and when one batch
@@ -304,7 +294,7 @@ void add_sized(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, c
   } else {
     const size_t soa = (size_t)(n + 1) * 16, per = sized_chain_lds(n);
     const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
-    const int waves = lds_waves(a.chains, soa, per, lim, cus);
+    const int waves = sa::lds_shape(a.chains, soa, per, lim, cus).waves;
     if (waves > 0) {
       const size_t lds = soa + per * waves;
       const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
@@ -508,18 +498,20 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
       const size_t soa = (size_t)(n + 1) * 16;
       const size_t per = lg == 6 ? wave_chain_lds(n, B) : static_wave_lds(n, B);
       const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
-      const int waves = lds_waves(a.chains, soa, per, lim, cus);
-      if (waves >= 4 || (waves > 0 && (int64_t)waves * cus >= a.chains)) {
+      const sa::LdsShape shape = sa::lds_shape(a.chains, soa, per, lim, cus);
+      if (sa::lds_suffices(shape, a.chains, cus)) {
+        const int waves = shape.waves;
         const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)B + 1};
         const size_t lds = soa + per * waves;
         if (rows_pay(n, B)) {
           // the limit-row kernel when the whole timeline fits 32 bits (its chains take a
           // little more LDS: the order carries 64 spare entries)
           const size_t rper = sa::rows_chain_bytes(n, B);
-          const int rwaves = lds_waves(a.chains, soa, rper, lim, cus);
+          const sa::LdsShape rshape = sa::lds_shape(a.chains, soa, rper, lim, cus);
+          const int rwaves = rshape.waves;
           const size_t rlds = soa + rper * rwaves;
           const int rows = sa::limit_rows_for((n + B - 1) / B);
-          if (rwaves >= 4 || (rwaves > 0 && (int64_t)rwaves * cus >= a.chains))
+          if (sa::lds_suffices(rshape, a.chains, cus))
             c.add(kSN | kT32, kAnnealFlags, [=](const sa::DevModel &d) {
               switch (rows) {
                 case 8: return launch_rows<OBJ, 8>(rwaves, rlds, d, sp, a);
@@ -551,7 +543,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
                          (ls ? ((sa::cont_ls_scratch_bytes(n) + 15) & ~size_t(15)) : 0) +
                          (inc ? sa::cont_inc_bytes(n, B) : 0);
       const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
-      const int waves = lds_waves(a.chains, soa, per, lim, cus);
+      const int waves = sa::lds_shape(a.chains, soa, per, lim, cus).waves;
       if (waves == 0) continue;
       const size_t lds = soa + per * waves;
       const int grid = (a.chains + waves - 1) / waves;
@@ -1143,7 +1135,7 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
   {
     // member times in 32 bits: windows restarted at the first change
     const size_t soa = (size_t)n * 16, per = sa::fit_chain_bytes(n);
-    const int waves = lds_waves(chains, soa, per, max_lds_per_block(), std::max(1, cu_count()));
+    const int waves = sa::lds_shape(chains, soa, per, max_lds_per_block(), std::max(1, cu_count())).waves;
     if (waves > 0) {
       const size_t lds = soa + per * waves;
       const int grid = (chains + waves - 1) / waves;

@@ -1,0 +1,51 @@
+"""Which kernel a call runs and the workgroup shapes it launches them in, against the oracle.
+
+The list of candidate kernels depends on sizes and settings only, so the index of the last one
+(the one without needs), which sched_status reports when no other's widths hold, says how many
+were listed."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+from gpu_helpers import oracle_chains  # noqa: E402
+
+from paper_2504_14966_amd.workloads import Model, random_queue  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+COEF = dict(p0=2000, p1=40, d0=8000, d1=300, d2=2)
+WIDE = dict(COEF, d0=1 << 24)  # a coefficient beyond the 24 bits that every static delta kernel needs
+
+
+@pytest.fixture(scope="module")
+def sl():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2504_14966_amd.sloanneal as m
+    m.load_library()
+    return m
+
+
+def _selected(sl, ws):
+    status = sl.sched_status(ws).cpu().tolist()
+    assert status[0] == 0, status
+    return status[2]
+
+
+@pytest.mark.parametrize("n,B,chains", [(900, 4, 1500), (300, 1, 1500), (600, 2, 1200), (1024, 4, 2200), (700, 3, 1300)])
+def test_delta_kernel_in_workgroups_of_three(sl, orc, n, B, chains):
+    # the LDS holds four or five chains, and three of them spread the chains evenly
+    rng = np.random.default_rng(n + B)
+    q = random_queue(rng, n, max_in=100, max_out=20, thr_hi=40_000 * n)
+    dq, m = sl.DeviceQueue.from_queue(q), Model(B, 0, **COEF)
+    assert _selected(sl, sl.sched_anneal(dq, Model(B, 0, **WIDE), chains, 1, 0.7, 0.99, 3)) == 1
+    ws = sl.sched_anneal(dq, m, chains, 60, 0.7, 0.99, 3)
+    assert _selected(sl, ws) == 0
+    rec, cur, best = sl.sched_chains(ws, n, chains, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    for c, (r, cu, be) in oracle_chains(q, m, [0, 1, 2, chains // 2, chains - 1], 60, 0.7, 0.99, 3, orc.start(q, m)).items():
+        assert np.array_equal(rec[c], r), c
+        assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c

@@ -1,0 +1,75 @@
+"""Workgroup shapes of the kernels with a block of LDS per chain (host arithmetic, compiled with g++)."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_14966_amd", "csrc")
+LIM, CUS = 160 * 1024, 256
+
+SHIM = r"""
+#include "launch_shape.h"
+extern "C" void shapes(long k, const int *chains, const long *shared, const long *per, int lim, int cus, int *out) {
+  for (long i = 0; i < k; ++i) {
+    const sa::LdsShape s = sa::lds_shape(chains[i], (size_t)shared[i], (size_t)per[i], lim, cus);
+    out[3 * i] = s.fit;
+    out[3 * i + 1] = s.waves;
+    out[3 * i + 2] = sa::lds_suffices(s, chains[i], cus);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shape")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+
+    def call(chains, shared, per):
+        chains, shared, per = np.broadcast_arrays(chains, shared, per)
+        c, s, p = (np.ascontiguousarray(a, t) for a, t in ((chains, np.int32), (shared, np.int64), (per, np.int64)))
+        out = np.zeros((c.size, 3), np.int32)
+        lib.shapes(C.c_long(c.size), c.ctypes, s.ctypes, p.ctypes, LIM, CUS, out.ctypes)
+        return tuple(out.reshape(c.shape + (3,)).transpose(-1, *range(c.ndim)))
+    return call
+
+
+def _static_chain_bytes(n, B):
+    """LDS of one chain of the kernel with several batches per row: the order (u16), the finish
+    offsets (u32, a spare one) and two 48-byte records per batch."""
+    return (2 * n + 15) // 16 * 16 + (4 * (n + 1) + 15) // 16 * 16 + 2 * 48 * -(-n // B)
+
+
+def test_delta_kernels_keep_what_power_of_two_workgroups_gave_them(shapes):
+    """Workgroups of 1, 2, 4, 8 or 16 chains were accepted when they held four chains or when one
+    pass held every chain. Every such call keeps the delta kernel, whatever count spreads its chains:
+    1500 chains where five fit go as workgroups of three."""
+    per = np.arange(1000, 60000, 331)[:, None, None]
+    shared = np.array([1056, 4816, 9616, 14416, 16400])[None, :, None]
+    chains = np.concatenate([np.arange(1, 2400, 7), np.arange(2400, 9000, 97)])[None, None, :]
+    full = np.broadcast_arrays(chains, shared, per)
+    waves = np.ones(full[0].shape, np.int64)
+    for _ in range(4):
+        waves = np.where((waves < 16) & (waves * CUS < full[0]), waves * 2, waves)
+    for _ in range(4):
+        waves = np.where((waves > 1) & (full[1] + full[2] * waves > LIM), waves // 2, waves)
+    was = (full[1] + full[2] * waves <= LIM) & ((waves >= 4) | (waves * CUS >= full[0]))
+    fit, spread, now = shapes(chains, shared, per)
+    assert was.any() and (~was).any()
+    assert not (was & (now == 0)).any()
+    # never more chains in a workgroup than fit, and enough workgroups in the passes for all
+    assert ((spread >= 1) == (fit >= 1)).all() and (spread <= fit).all() and (fit <= 16).all()
+    held = fit > 0
+    passes = np.where(held, -(-full[0] // np.maximum(fit * CUS, 1)), 1)
+    assert (spread * passes * CUS >= full[0])[held].all()
+
+
+@pytest.mark.parametrize("n,B,chains", [(900, 4, 1500), (300, 1, 1500), (600, 2, 1200), (1024, 4, 2200), (700, 3, 1300)])
+def test_delta_kernel_sizes_where_the_spread_is_three(shapes, n, B, chains):
+    fit, waves, now = shapes(chains, 16 * (n + 1), _static_chain_bytes(n, B))
+    assert fit in (4, 5) and waves == 3 and now == 1
