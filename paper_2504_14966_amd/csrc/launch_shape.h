@@ -1,5 +1,6 @@
-// Workgroup shapes of the kernels that keep a block of LDS per chain behind records shared by the
-// workgroup. Host arithmetic only, with no HIP in it.
+// Workgroup shapes: the annealing kernels that keep a block of LDS per chain behind records shared
+// by the workgroup, and the one-order-per-wave evaluation kernels. Host arithmetic only, with no
+// HIP in it.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -27,6 +28,28 @@ inline LdsShape lds_shape(int chains, size_t shared, size_t per, int lim, int cu
 // spread: 1500 chains where five fit go as 500 workgroups of three.
 inline bool lds_suffices(const LdsShape &s, int chains, int cus) {
   return s.fit >= 4 || (s.fit > 0 && (int64_t)s.fit * cus >= chains);
+}
+
+// Workgroups of a one-order-per-wave evaluation. Each forms the verdict and stages the requests
+// first, about 3 us, so no more than `held`, what the GPU holds at once, with every wave taking
+// several rows: at 32768 rows of 10 requests, 8192 workgroups took 56 us and 2048 take 25 us.
+// Workgroups all resident end unevenly over many rows, though, so from four rows per wave on one
+// workgroup per 4 `waves` rows (at most 8192), which start as others end: 2^20 rows of 128
+// requests take 678 us in 2048 workgroups, 551 us in 8192. Between the two, a count a little
+// above `held` leaves a last pass nearly empty (4500 continuous rows of 700 requests in batches
+// of 64, one workgroup per CU: 1125 workgroups 240 us, 281 352 us, 256 222 us; 32768 layouts of
+// 400 requests in batches of up to 64, seven per CU: 8192 313 us, 2048 404 us, 1792 288 us): `beyond` times `held` must be passed.
+// `per_simd` is what the kernel's registers allow; a CU has four SIMDs.
+struct EvalShape {
+  int per_simd;
+  double beyond;
+};
+inline int eval_grid(int64_t rows, int waves, size_t lds, const EvalShape &k, int lim, int cus) {
+  const int64_t per_cu =
+      std::max<int64_t>(1, std::min<int64_t>(4 * k.per_simd / waves, (int64_t)lim / (int64_t)lds));
+  const int64_t held = per_cu * cus, want = (rows + waves - 1) / waves;
+  const int64_t more = std::min<int64_t>(8192, rows / (4 * waves));
+  return (int)std::min<int64_t>(want, (double)more >= k.beyond * (double)held ? more : held);
 }
 
 }  // namespace sa

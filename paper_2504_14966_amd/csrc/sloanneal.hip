@@ -213,15 +213,16 @@ Limits device_limits() {
   return l;
 }
 
-// Workgroups of an evaluation launch. Each forms the verdict and stages the requests first,
-// about 3 us: at 32768 rows of 10 requests, 8192 workgroups took 56 us and 2048 (what the GPU
-// holds at once) 25 us. Beyond that as many as leave every wave four rows, at most 8192: with
-// 2^20 rows of 128 requests, 2048 workgroups end unevenly (eval_static_kernel 678 us against
-// 551 us), and at 131072 rows of 400 requests 2048 take 376 us, 8192 take 332 us.
-int eval_grid(int64_t rows, int waves, size_t lds, const Limits &dl) {
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32 / waves, (int64_t)dl.lds / (int64_t)(lds + sa::kCheckLdsBytes)));
-  const int64_t most = std::max<int64_t>(per_cu * dl.cus, std::min<int64_t>(8192, rows / (4 * waves)));
-  return (int)std::min<int64_t>((rows + waves - 1) / waves, most);
+// The one-order-per-wave evaluation kernels: waves per SIMD that their registers allow, and from
+// how many times the resident workgroups on more are launched. The replays that are bound by
+// latency (continuous admission, layouts: a gather per batch member) lose less to an uneven end,
+// so theirs lies higher: 4500 continuous rows of 1024 requests take 388 us in the 256 workgroups
+// held at once and 517 us in 562 (2.2 times that), while 65536 rows of 400 requests take 243 us
+// resident and 221 us in 4096 (2.3 times) on the static kernel, 197 and 170 us on the fitted one.
+constexpr sa::EvalShape kEvalStatic{8, 1.5}, kEvalFit{7, 1.5}, kEvalLayouts{7, 2.5}, kEvalAny{5, 2.5};
+
+int eval_workgroups(int64_t rows, int waves, size_t lds, const sa::EvalShape &k, const Limits &dl) {
+  return sa::eval_grid(rows, waves, lds + sa::kCheckLdsBytes, k, dl.lds, dl.cus);
 }
 
 size_t sized_chain_lds(int n) {
@@ -824,7 +825,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
     while ((1 << lg) < model->max_batch) ++lg;
     const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)model->max_batch + 1};
     const size_t lds = (size_t)(n + 1) * 16 + ((((size_t)n * 2 + 15) & ~size_t(15)) + 64 * 8 + 32 * 4) * 4;
-    const int g4 = eval_grid(k, 4, lds, dl);
+    const int g4 = eval_workgroups(k, 4, lds, kEvalStatic, dl);
     if (!detail) add_eval_lanes<false>(c, model, n, qp, perms, nullptr, k, out, dl, stream);
     c.add(kSN, kEvalFlags | kT32, [=](const sa::DevModel &d) {
 #define SA_EVAL_CASE(L)                                                                            \
@@ -856,7 +857,7 @@ int sched_eval(const sched_queue_t *queue, const sched_model_t *model, const uin
   int waves = sa::kWavesPerBlock;
   while (waves > 1 && eval_lds_bytes(n, ls, waves) > lim) waves >>= 1;
   const size_t lds = eval_lds_bytes(n, ls, waves);
-  const int grid = eval_grid(k, waves, lds, dl);
+  const int grid = eval_workgroups(k, waves, lds, kEvalAny, dl);
   c.add(0u, kEvalFlags, [=](const sa::DevModel &d) {
     const void *fn = detail ? (const void *)&sa::eval_kernel<true> : (const void *)&sa::eval_kernel<false>;
     if (lds > 65536) {
@@ -973,7 +974,7 @@ int sched_eval_batches(const sched_queue_t *queue, const sched_model_t *model, c
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * sa::sized_row_bytes(n);
   const Limits dl = device_limits();
-  const int grid = eval_grid(k, 4, lds, dl);
+  const int grid = eval_workgroups(k, 4, lds, kEvalLayouts, dl);
   Candidates<sa::DevModel> c;
   if (!detail) add_eval_lanes<true>(c, model, n, qp, perms, starts, k, out, dl, stream);
   // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
@@ -1086,7 +1087,7 @@ int sched_eval_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, con
   const sa::QueuePtrs qp = dev_queue(queue);
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (pb + fb + 32 * 4);
-  const int grid = eval_grid(k, 4, lds, device_limits());
+  const int grid = eval_workgroups(k, 4, lds, kEvalFit, device_limits());
   Candidates<sa::DevFit> c;
   c.add(0u, sa::kFlagFitWindows, [=](const sa::DevFit &d) {
     if (detail)

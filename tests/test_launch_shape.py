@@ -73,3 +73,44 @@ def test_delta_kernels_keep_what_power_of_two_workgroups_gave_them(shapes):
 def test_delta_kernel_sizes_where_the_spread_is_three(shapes, n, B, chains):
     fit, waves, now = shapes(chains, 16 * (n + 1), _static_chain_bytes(n, B))
     assert fit in (4, 5) and waves == 3 and now == 1
+
+
+EVAL_SHIM = r"""
+#include "launch_shape.h"
+extern "C" int grid(long rows, int waves, long lds, int per_simd, double beyond, int lim, int cus) {
+  return sa::eval_grid(rows, waves, (size_t)lds, sa::EvalShape{per_simd, beyond}, lim, cus);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def eval_grid(tmp_path_factory):
+    d = tmp_path_factory.mktemp("grid")
+    (d / "shim.cpp").write_text(EVAL_SHIM)
+    so = str(d / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    lib.grid.argtypes = [C.c_long, C.c_int, C.c_long, C.c_int, C.c_double, C.c_int, C.c_int]
+    return lambda rows, waves, lds, per_simd, beyond: lib.grid(rows, waves, lds, per_simd, beyond, LIM, CUS)
+
+
+# (per SIMD, beyond, waves, LDS of a workgroup, held at once): the static, fitted, layout and any-width
+# kernels at short and long queues
+@pytest.mark.parametrize("per_simd,beyond,waves,lds,held", [(8, 1.5, 4, 2304, 2048), (8, 1.5, 4, 32384, 1280),
+                                                            (7, 1.5, 4, 6144, 1792), (7, 2.5, 4, 14000, 1792),
+                                                            (5, 2.5, 4, 6000, 1280), (5, 2.5, 4, 91000, 256),
+                                                            (5, 2.5, 2, 122000, 256), (5, 2.5, 2, 40000, 1024)])
+def test_eval_workgroups_leave_no_thin_last_pass(eval_grid, per_simd, beyond, waves, lds, held):
+    """Rows in workgroups held at once, or enough workgroups beyond them: a count a little above what
+    the GPU holds (registers and LDS) waits for a last pass that is nearly empty."""
+    for rows in sorted({1, 3, 4, 5, 255 * waves, held * waves, held * waves + 1, *range(700, 400000, 911), 1 << 20, 1 << 24}):
+        g, want = eval_grid(rows, waves, lds, per_simd, beyond), -(-rows // waves)
+        assert 1 <= g <= want and g <= max(8192, held), rows
+        assert g == want if want <= held else (g == held or g >= beyond * held), (rows, g)
+
+
+def test_eval_workgroups_of_measured_calls(eval_grid):
+    assert eval_grid(4500, 4, 91136, 5, 2.5) == 256    # continuous, 700 requests: 281 took 1.6 times as long
+    assert eval_grid(32768, 4, 14144, 7, 2.5) == 1792  # layouts, 400 requests: 2048 took 1.4 times as long
+    assert eval_grid(32768, 4, 1500, 8, 1.5) == 2048   # 10 requests: 8192 took twice as long
+    assert eval_grid(1 << 20, 4, 8000, 8, 1.5) == 8192
