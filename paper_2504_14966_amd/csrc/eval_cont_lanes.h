@@ -47,7 +47,7 @@ template <int CAP>
 __global__ void __launch_bounds__(256) eval_cont_lanes_kernel(DevModel m, QueuePtrs q, const uint16_t *__restrict__ perms,
                                                                int64_t rows, int64_t *__restrict__ out) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const EvalRows span = eval_gate(q, m, rows, out);
+  const EvalRows span = eval_gate<true>(q, m, rows, out);
   if (span.end <= span.begin) return;
   const int n = m.n, n0 = min(m.B, n), nadm = n - n0, lane = lane_id();
   const uint32_t d0 = (uint32_t)m.d0, d1 = (uint32_t)m.d1, d2 = (uint32_t)m.d2;

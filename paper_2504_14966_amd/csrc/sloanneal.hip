@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <functional>
@@ -190,28 +191,34 @@ size_t eval_lds_bytes(int n, bool ls, int waves) {
 size_t static_wave_lds(int n, int B) { return sa::static_chain_bytes(n, B); }
 size_t wave_chain_lds(int n, int B) { return sa::wave_chain_bytes(n, B); }
 
-int device_attr(hipDeviceAttribute_t attr, int fallback) {
-  int dev = 0, v = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, attr, dev) != hipSuccess) return fallback;
-  return v;
-}
-int max_lds_per_block() { return device_attr(hipDeviceAttributeMaxSharedMemoryPerBlock, 65536); }
-int cu_count() { return device_attr(hipDeviceAttributeMultiprocessorCount, 256); }
+constexpr int kMaxDevices = 64;
 
-// Both for the current device, asked for once per evaluation call: a small one is bound by the
-// host's launch, and asking up to seven times took 16 continuous rows of 24 requests 10.1 us
-// where this takes 9.5 us.
+// LDS per workgroup and CUs of the current device. They never change, so each device is asked once
+// and the answer kept: a small evaluation call is bound by the host's launch, and two lookups in
+// each took layouts and fitted rows of a short queue 9.6 and 11.2 us where these take 9.3 and 10.8.
 struct Limits {
   int lds = 65536, cus = 256;
 };
+std::atomic<uint64_t> g_limits[kMaxDevices];  // lds << 32 | cus; 0: not asked yet
+
 Limits device_limits() {
   Limits l;
-  int dev = 0, v = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return l;
-  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) l.lds = v;
-  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) l.cus = std::max(1, v);
+  int dev = 0, lds = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return l;
+  uint64_t v = g_limits[dev].load(std::memory_order_relaxed);
+  if (v == 0) {
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || lds < 1 ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      return l;
+    v = (uint64_t)(uint32_t)lds << 32 | (uint32_t)cus;
+    g_limits[dev].store(v, std::memory_order_relaxed);
+  }
+  l.lds = (int)(v >> 32);
+  l.cus = (int)(uint32_t)v;
   return l;
 }
+int max_lds_per_block() { return device_limits().lds; }
+int cu_count() { return device_limits().cus; }
 
 // The one-order-per-wave evaluation kernels: waves per SIMD that their registers allow, and from
 // how many times the resident workgroups on more are launched. The replays that are bound by
@@ -246,7 +253,7 @@ bool reg_any_pays(int n, int B) { return B <= 32 && n > B; }
 // Chains per workgroup of the register kernels: four, or fewer so that the chains spread
 // over every CU.
 int reg_waves(int chains) {
-  const int cus = std::max(1, cu_count());
+  const int cus = cu_count();
   return chains >= 4 * cus ? 4 : (chains >= 2 * cus ? 2 : 1);
 }
 
@@ -294,7 +301,7 @@ void add_sized(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, c
     });
   } else {
     const size_t soa = (size_t)(n + 1) * 16, per = sized_chain_lds(n);
-    const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
+    const int lim = max_lds_per_block(), cus = cu_count();
     const int waves = sa::lds_shape(a.chains, soa, per, lim, cus).waves;
     if (waves > 0) {
       const size_t lds = soa + per * waves;
@@ -394,7 +401,7 @@ hipError_t launch_static(int waves, size_t lds, const sa::DevModel &d, const sa:
 // 7.0 / 7.0 ms, 1024 chains 8.7 / 9.2 / 13.1 ms). `any`: two waves whenever they fit at all.
 template <int OBJ>
 int spec_waves(int n, int B, int chains, bool any = false) {
-  const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
+  const int cus = cu_count(), lim = max_lds_per_block();
   auto resident = [&](const void *fn, int W) {  // workgroups the GPU holds at once
     const size_t lds = sa::spec_chain_bytes(n, B, W);
     int nb = 0;
@@ -498,7 +505,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
       while ((1 << lg) < B) ++lg;
       const size_t soa = (size_t)(n + 1) * 16;
       const size_t per = lg == 6 ? wave_chain_lds(n, B) : static_wave_lds(n, B);
-      const int lim = max_lds_per_block(), cus = std::max(1, cu_count());
+      const int lim = max_lds_per_block(), cus = cu_count();
       const sa::LdsShape shape = sa::lds_shape(a.chains, soa, per, lim, cus);
       if (sa::lds_suffices(shape, a.chains, cus)) {
         const int waves = shape.waves;
@@ -543,7 +550,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
       const size_t per = (((size_t)n * 2 + 15) & ~size_t(15)) +
                          (ls ? ((sa::cont_ls_scratch_bytes(n) + 15) & ~size_t(15)) : 0) +
                          (inc ? sa::cont_inc_bytes(n, B) : 0);
-      const int cus = std::max(1, cu_count()), lim = max_lds_per_block();
+      const int cus = cu_count(), lim = max_lds_per_block();
       const int waves = sa::lds_shape(a.chains, soa, per, lim, cus).waves;
       if (waves == 0) continue;
       const size_t lds = soa + per * waves;
@@ -638,7 +645,7 @@ hipError_t launch_multi_cont(size_t lds, const sa::DevModel &d, const MultiArgs 
 template <int OBJ>
 void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const MultiArgs &a) {
   const int B = model->max_batch, n = a.n, total = a.instances * a.chains;
-  const int cus = std::max(1, cu_count());
+  const int cus = cu_count();
   if (model->policy == SCHED_STATIC &&
       (sa::reg_form(B) != sa::kRegAny || reg_any_pays((n + a.instances - 1) / a.instances, B))) {
     const int waves = total >= 4 * cus && a.chains >= 4 ? 4 : (total >= 2 * cus && a.chains >= 2 ? 2 : 1);
@@ -780,7 +787,6 @@ void add_eval_cont_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model
 // the symbol); it uses the device address obtained once per device below.
 static __device__ __align__(256) unsigned char scratch[SCHED_NOALLOC_MAX_BYTES];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
 
@@ -1136,7 +1142,7 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
   {
     // member times in 32 bits: windows restarted at the first change
     const size_t soa = (size_t)n * 16, per = sa::fit_chain_bytes(n);
-    const int waves = sa::lds_shape(chains, soa, per, max_lds_per_block(), std::max(1, cu_count())).waves;
+    const int waves = sa::lds_shape(chains, soa, per, max_lds_per_block(), cu_count()).waves;
     if (waves > 0) {
       const size_t lds = soa + per * waves;
       const int grid = (chains + waves - 1) / waves;
