@@ -257,9 +257,6 @@ __device__ Score replay_fit_windows32(const DevFit &f, const uint4 *__restrict__
 template <bool DETAIL>
 __device__ __forceinline__ Score replay_fit(const DevFit &f, const uint4 *__restrict__ req, const uint16_t *perm,
                                             const uint8_t *flags, int64_t *detail) {
-  if constexpr (!DETAIL) {
-    if (f.m32) return replay_fit_windows32(f, req, perm, flags);
-  }
   if (f.win) return replay_fit_windows<DETAIL>(f, req, perm, flags, detail);
   return replay_fit_batches<DETAIL>(f, req, perm, flags, detail);
 }
@@ -379,8 +376,10 @@ __global__ void __launch_bounds__(1024) start_fit_kernel(DevFit f, QueuePtrs q, 
     }
   }
   if (tid < 64) {
-    const Score sorted = replay_fit<false>(f, req, key_id, nullptr, nullptr);
-    const Score input = replay_fit<false>(f, req, ident, nullptr, nullptr);
+    auto score = [&](const uint16_t *order) {
+      return f.m32 ? replay_fit_windows32(f, req, order, nullptr) : replay_fit<false>(f, req, order, nullptr, nullptr);
+    };
+    const Score sorted = score(key_id), input = score(ident);
     const bool input_better = srch.objective ? obj_better<1>(input.n, input.t, sorted.n, sorted.t)
                                              : obj_better<0>(input.n, input.t, sorted.n, sorted.t);
     const bool use_input = !(srch.early_exit && sorted.n == n) && input_better;
@@ -642,9 +641,10 @@ __global__ void __launch_bounds__(1024) anneal_fit_windows_kernel(DevFit f, Queu
   if (lane == 0) write_record(ws, n, chain, cn, ct, bn, bt, biter, accepts, digest, allmet);
 }
 
-// One wave per chain, four per workgroup; full replay per proposal. Fixed-size batches take
-// swap / insert proposals (swap iff w0 < swap_thr); the batch-size search takes squeeze /
-// delay / swap. Per-wave LDS: current and candidate orders and flags.
+// Member times beyond 32 bits (up to 64 requests: a timeline of 2^57 or more). One wave per chain,
+// four per workgroup; full replay per proposal. Fixed-size batches take swap / insert proposals
+// (swap iff w0 < swap_thr); the batch-size search takes squeeze / delay / swap. Per-wave LDS:
+// current and candidate orders and flags.
 template <int OBJ>
 __global__ void __launch_bounds__(256) anneal_fit_kernel(DevFit f, QueuePtrs q, const uint32_t *thr2, int chains,
                                                           int iters, double T0, double alpha, uint32_t key0,

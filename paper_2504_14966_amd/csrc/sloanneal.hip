@@ -1138,9 +1138,10 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
                                                                       k1, st, srch, w);
       return hipGetLastError();
     });
-  }
-  {
-    // member times in 32 bits: windows restarted at the first change
+  } else {
+    // member times in 32 bits: windows restarted at the first change (of up to 64 requests such
+    // times sum to below 2^38 and the kernel above runs: listing this one too added a launch that
+    // returned at once, 4 us of 60)
     const size_t soa = (size_t)n * 16, per = sa::fit_chain_bytes(n);
     const int waves = sa::lds_shape(chains, soa, per, max_lds_per_block(), cu_count()).waves;
     if (waves > 0) {
@@ -1163,7 +1164,7 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
   const size_t pb = ((size_t)n * 2 + 15) & ~size_t(15), fb = ((size_t)n + 15) & ~size_t(15);
   const size_t lds = (((size_t)n * 16 + 15) & ~size_t(15)) + 4 * (2 * pb + 2 * fb);
   const int grid = (chains + 3) / 4;
-  c.add(0u, kFitFlags, [=](const sa::DevFit &d) {
+  c.add(0u, sa::kFlagFitWindows, [=](const sa::DevFit &d) {
     if (srch.objective)
       sa::anneal_fit_kernel<1><<<grid, 256, lds, stream>>>(d, qp, tpot_thr, chains, iters, T0, alpha, k0, k1, st, srch,
                                                            w);

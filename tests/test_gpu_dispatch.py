@@ -49,3 +49,24 @@ def test_delta_kernel_in_workgroups_of_three(sl, orc, n, B, chains):
     for c, (r, cu, be) in oracle_chains(q, m, [0, 1, 2, chains // 2, chains - 1], 60, 0.7, 0.99, 3, orc.start(q, m)).items():
         assert np.array_equal(rec[c], r), c
         assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
+
+
+# (requests, fixed prefill cost, kernel that runs): the register kernel and the full replay for up to
+# 64 requests; the restarted windows and the full replay above
+@pytest.mark.parametrize("n,dp,selected", [(3, 4000, 0), (64, 1 << 40, 0), (3, 1 << 56, 1), (65, 4000, 0), (65, 1 << 40, 1),
+                                           (130, 1 << 36, 1)])
+@pytest.mark.parametrize("policy", [0, 2])
+def test_fitted_candidates(sl, orc, n, dp, selected, policy):
+    rng = np.random.default_rng(n + policy)
+    q = random_queue(rng, n, max_in=1000, max_out=100, thr_hi=2**32 - 2)
+    coef = dict(ap=3, bp=5, cp=7, dp=dp, ad=1, bd=2, cd=3, dd=11)
+    fd, fo = sl.FitModel(4, policy, **coef), orc.FitModel(4, policy, **coef)
+    ws = sl.sched_anneal_fit(sl.DeviceQueue.from_queue(q), fd, 5, 120, 0.5, 0.99, 3)
+    assert _selected(sl, ws) == selected
+    rec, cur, best = sl.sched_chains(ws, n, 5, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    info = orc.start_fit(q, fo)
+    for c in range(5):
+        w = orc.anneal_chain_fit(q, fo, c, 120, 0.5, 0.99, 3, start_info=info)
+        assert np.array_equal(rec[c], w["rec"]), c
+        assert np.array_equal(cur[c], w["cur"]) and np.array_equal(best[c], w["best"]), c
