@@ -82,6 +82,8 @@ constexpr int kFlagInst192 = 512;      // several instances: each holds at most 
 // evaluation calls only (no workspace header ever holds it)
 constexpr int kFlagEvalLaneSums = 1024;  // one order per lane, static: 24-bit factors of a batch's running sums
 constexpr int kFlagEvalLaneCont = 2048;  // one order per lane, continuous: 24-bit factors of the segment costs
+// set by the kernel that forms the start order, for the choice of the kernel only (no header holds it)
+constexpr int kFlagHotScale = 4096;  // the Metropolis scale keeps a run hot (scale_keeps_hot)
 constexpr uint64_t kWsMagic = 0x534c4f414e4e3031ull;  // "SLOANN01"
 
 __host__ __device__ __forceinline__ size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

@@ -106,8 +106,9 @@ __device__ __forceinline__ bool key_better(int64_t n1, uint64_t t1, int64_t n2, 
   return n1 > n2 || (n1 == n2 && t1 < t2);
 }
 
-// Algorithm 1 initialisation by one workgroup of 1024 threads; n <= 1024.
-__device__ void start_body(const DevModel &m, const QueuePtrs &q, int chains, int iters, int64_t t_ref_user,
+// Algorithm 1 initialisation by one workgroup of 1024 threads; n <= 1024. Returns the input order's
+// total latency (in the first wave).
+__device__ uint64_t start_body(const DevModel &m, const QueuePtrs &q, int chains, int iters, int64_t t_ref_user,
                            const SearchParams &srch, unsigned char *ws) {
   __shared__ uint4 req[1024];
   __shared__ uint64_t key_solo[1024];
@@ -153,9 +154,11 @@ __device__ void start_body(const DevModel &m, const QueuePtrs &q, int chains, in
       __syncthreads();
     }
   }
+  uint64_t t_in = 0;
   if (tid < 64) {
     const Score sorted = replay<false>(m, req, key_id, Remap{0, 0, 0}, stage, nullptr);
     const Score input = replay<false>(m, req, ident, Remap{0, 0, 0}, stage, nullptr);
+    t_in = input.t;
     // the better of the two starts; with the early exit, a sorted order that meets every
     // SLO is the result itself
     const bool input_better = srch.objective ? obj_better<1>(input.n, input.t, sorted.n, sorted.t)
@@ -183,20 +186,28 @@ __device__ void start_body(const DevModel &m, const QueuePtrs &q, int chains, in
       h->best_t = -1;
     }
   }
+  return t_in;
 }
 
 // The first kernel of a single-queue annealing call: the device checks of the queue (their
-// verdict goes to the header; a failed check ends the call here), then the start order.
+// verdict goes to the header; a failed check ends the call here), then the start order. T_low: the
+// lowest temperature of the call's proposals.
 __global__ void __launch_bounds__(1024) start_kernel(DevModel m, QueuePtrs q, int chains, int iters,
-                                                      int64_t t_ref_user, SearchParams srch, unsigned char *ws) {
-  const Plan p = plan_in_block(q, m);
+                                                      int64_t t_ref_user, double T_low, SearchParams srch,
+                                                      unsigned char *ws) {
+  Plan p = plan_in_block(q, m);
   if (p.status != 0) {
     if (threadIdx.x == 0) write_failed_header(ws, p, m.n, chains, iters, m.policy, m.B);
     return;
   }
-  if (threadIdx.x == 0) write_plan(ws, p);
-  m.flags |= (int32_t)(p.flags & m.gate.allow);
-  start_body(m, q, chains, iters, t_ref_user, srch, ws);
+  const Gate gate = m.gate;
+  m.flags |= (int32_t)(p.flags & gate.allow);
+  const uint64_t t_in = start_body(m, q, chains, iters, t_ref_user, srch, ws);
+  if (threadIdx.x == 0) {
+    if (scale_keeps_hot(T_low, t_ref_user, t_in, srch.objective))
+      p.selected = plan_select(gate, p.flags | kFlagHotScale);
+    write_plan(ws, p);
+  }
 }
 
 // One chain by one wave, full replay per proposal: the chain's record slot is `chain`, its

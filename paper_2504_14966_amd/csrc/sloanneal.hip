@@ -342,15 +342,18 @@ hipError_t launch_reg(bool parts, int grid, int waves, const sa::DevModel &d, co
   return hipGetLastError();
 }
 
-// Whether a run stays so hot that most proposals are kept: the temperature of its last proposal
-// is at least 4, where a candidate that loses one of the met requests (an energy gap of about 1)
-// is still kept with probability 0.78. The paper's schedule ends at 20. (One of 8 or more chains
-// of 10 requests cooled from 1 to 0.01 keeps 59 %: with four proposals per round it took
-// 1.2 ms per 2000 proposals where the register kernel takes 1.0 ms.)
-bool stays_hot(const ChainArgs &a) {
+// Lowest temperature of a call's proposals.
+double lowest_temperature(const ChainArgs &a) {
   const double levels = a.iters > 0 ? (double)((a.iters - 1) / a.srch.level_len) : 0.0;
-  return a.T0 >= 4.0 && a.T0 * std::pow(a.alpha, levels) >= 4.0;
+  return std::min(a.T0, a.T0 * std::pow(a.alpha, levels));
 }
+// Whether a run stays so hot that most proposals are kept: at 4 a candidate that loses one of the
+// met requests (an energy gap of about 1) is still kept with probability 0.78. The paper's schedule
+// ends at 20. (One of 8 or more chains of 10 requests cooled from 1 to 0.01 keeps 59 %: with four
+// proposals per round it took 1.2 ms per 2000 proposals where the register kernel takes 1.0 ms.)
+// That holds on the queue's own scale; with a t_ref of the caller's the device decides
+// (kFlagHotScale).
+bool stays_hot(const ChainArgs &a) { return lowest_temperature(a) >= 4.0; }
 
 // One batch per wave with limit rows (timelines of 32 bits): batches of 17 and more, at most 32
 // of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
@@ -472,7 +475,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
     if (n <= 16 && n > B && stays_hot(a)) {
       // 32-bit timelines: four proposals per round
       const int waves = reg_waves(a.chains), grid = (a.chains + waves - 1) / waves;
-      c.add(kSN | kT32, kAnnealFlags, [=](const sa::DevModel &d) {
+      c.add(kSN | kT32 | sa::kFlagHotScale, kAnnealFlags, [=](const sa::DevModel &d) {
         auto go = [&](auto kernel) {
           kernel<<<grid, waves * 64, 0, a.stream>>>(d, a.q, a.chains, a.iters, a.T0, a.alpha, a.k0, a.k1, a.swap_thr,
                                                     a.srch, a.w);
@@ -912,7 +915,8 @@ int sched_anneal_ex(const sched_queue_t *queue, const sched_model_t *model, cons
     add_chains<1>(c, model, n, a);
   else
     add_chains<0>(c, model, n, a);
-  sa::start_kernel<<<1, 1024, 0, stream>>>(c.checker(dm, kAnnealFlags), a.q, chains, iters, model->t_ref_us, srch, w);
+  sa::start_kernel<<<1, 1024, 0, stream>>>(c.checker(dm, kAnnealFlags), a.q, chains, iters, model->t_ref_us,
+                                           lowest_temperature(a), srch, w);
   HIP_TRY(hipGetLastError());
   if ((rc = c.run(dm))) return rc;
   sa::reduce_kernel<<<1, 1024, 0, stream>>>(w);

@@ -70,3 +70,25 @@ def test_fitted_candidates(sl, orc, n, dp, selected, policy):
         w = orc.anneal_chain_fit(q, fo, c, 120, 0.5, 0.99, 3, start_info=info)
         assert np.array_equal(rec[c], w["rec"]), c
         assert np.array_equal(cur[c], w["cur"]) and np.array_equal(best[c], w["best"]), c
+
+
+# the scale of the Metropolis test: the queue's own (0), and factors of the input order's total latency
+@pytest.mark.parametrize("ratio,factor,selected", [(0, 0.0, 0), (1, 0.0, 0), (0, 1.0, 0), (1, 1.0, 0), (0, 0.03, 0),
+                                                   (0, 0.02, 1), (0, 1e-4, 1), (0, 100.0, 0), (1, 3.9, 0), (1, 4.1, 1),
+                                                   (1, 1e4, 1), (1, 1e-3, 0)])
+def test_hot_chains_by_the_metropolis_scale(sl, orc, ratio, factor, selected):
+    # 4.0 at the last proposal: four proposals per round only where that temperature is hot
+    rng = np.random.default_rng(7)
+    n, B, iters = 10, 4, 202
+    q = random_queue(rng, n, max_in=2000, max_out=150, thr_hi=60_000 * n)
+    dq, m = sl.DeviceQueue.from_queue(q), Model(B, 0, **COEF)
+    m.t_ref_us = int(round(factor * orc.replay(q, m, np.arange(n, dtype=np.uint16))[1]))
+    search = (ratio, 1, 0)
+    ws = sl.sched_anneal(dq, m, 6, iters, 4.0, 1.0, 21, search=sl.Search(*search))
+    assert _selected(sl, ws) == selected
+    rec, cur, best = sl.sched_chains(ws, n, 6, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    info = orc.start(q, m, search=orc.Search(*search))
+    for c, (r, cu, be) in oracle_chains(q, m, range(6), iters, 4.0, 1.0, 21, info, search).items():
+        assert np.array_equal(rec[c], r), c
+        assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
