@@ -425,6 +425,11 @@ int spec_waves(int n, int B, int chains, bool any = false) {
   while (w1 > 1 && (size_t)n * 16 + per1 * w1 > (size_t)lim) w1 >>= 1;
   const size_t lds1 = (size_t)n * 16 + per1 * w1;
   const int64_t res1 = lds1 <= (size_t)lim ? (int64_t)w1 * std::max<int64_t>(1, lim / (int64_t)lds1) : 0;
+  // Above nine chains per CU the second proposals take issue slots that the first ones need: one
+  // wave per chain where the LDS holds all of them (64 requests, 16 running, 61 and 38 % kept: 3584
+  // chains in 0.82 and 0.77 of the time, 2560 in 0.91 and 0.84, 2048 in 0.98 and 0.91, 1024 in 1.13
+  // and 1.06).
+  if (chains > 9 * cus && chains <= res2 && chains <= res1 * cus) return 0;
   return res2 > 0 && std::min<int64_t>(chains, res2) >= std::min<int64_t>(chains, res1 * cus) ? 2 : 0;
 }
 

@@ -92,3 +92,23 @@ def test_hot_chains_by_the_metropolis_scale(sl, orc, ratio, factor, selected):
     for c, (r, cu, be) in oracle_chains(q, m, range(6), iters, 4.0, 1.0, 21, info, search).items():
         assert np.array_equal(rec[c], r), c
         assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
+
+
+# (requests, batch, chains, candidates before the last one): two waves per chain, one, the event loop;
+# above nine chains per CU the first only where one wave each would not fit at once
+@pytest.mark.parametrize("n,B,chains,before", [(64, 16, 2048, 3), (64, 16, 2304, 3), (64, 16, 2305, 2), (64, 16, 3300, 2),
+                                               (91, 6, 3357, 2), (200, 16, 3500, 3), (256, 32, 3000, 3)])
+def test_two_proposals_per_round_by_chains(sl, orc, n, B, chains, before):
+    rng = np.random.default_rng(n + chains)
+    q = random_queue(rng, n, max_in=100, max_out=20, thr_hi=40_000 * n)
+    dq = sl.DeviceQueue.from_queue(q)
+    wide = dict(COEF, d2=1 << 25)  # no 32-bit event arithmetic: the last candidate runs
+    assert _selected(sl, sl.sched_anneal(dq, Model(B, 1, t_ref_us=1, **wide), chains, 1, 0.7, 0.99, 3)) == before
+    m = Model(B, 1, **COEF)
+    ws = sl.sched_anneal(dq, m, chains, 40, 0.7, 0.99, 3)
+    assert _selected(sl, ws) == 0
+    rec, cur, best = sl.sched_chains(ws, n, chains, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    for c, (r, cu, be) in oracle_chains(q, m, [0, 5, chains // 2, chains - 1], 40, 0.7, 0.99, 3, orc.start(q, m)).items():
+        assert np.array_equal(rec[c], r), c
+        assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
