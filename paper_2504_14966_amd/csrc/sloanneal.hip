@@ -697,7 +697,12 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
       });
     }
   }
-  if (model->policy == SCHED_CONTINUOUS) {
+  // Instances of two or three requests have little to replay, and many chains leave no issue slots
+  // for second proposals: the full replay by one wave per chain is faster there (12 instances of
+  // 3, 929 chains each: 0.80 of the time; of 2 from about 1024 chains in all: 0.63 to 0.9; of 4 it
+  // loses, 1.0 to 2.4).
+  const bool tiny = (n <= 2 * a.instances && total > 4 * cus) || (n <= 3 * a.instances && total > 12 * cus);
+  if (model->policy == SCHED_CONTINUOUS && !tiny) {
     // list scheduling, 32-bit times: LDS for instances of at most 64 or 192 requests, or of
     // the whole queue (more waves per chain when the chains leave the GPU nearly empty)
     const uint32_t need = sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime;

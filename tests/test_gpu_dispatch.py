@@ -12,7 +12,7 @@ import pytest
 sys.path.insert(0, os.path.dirname(__file__))
 from gpu_helpers import oracle_chains  # noqa: E402
 
-from paper_2504_14966_amd.workloads import Model, random_queue  # noqa: E402
+from paper_2504_14966_amd.workloads import Model, Queue, random_queue  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +112,31 @@ def test_two_proposals_per_round_by_chains(sl, orc, n, B, chains, before):
     for c, (r, cu, be) in oracle_chains(q, m, [0, 5, chains // 2, chains - 1], 40, 0.7, 0.99, 3, orc.start(q, m)).items():
         assert np.array_equal(rec[c], r), c
         assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
+
+
+# (instances, requests, chains, candidates before the full replay): mean sizes of 2, 3 and 4
+@pytest.mark.parametrize("inst,n,chains,before", [(4, 8, 256, 1), (4, 8, 257, 0), (12, 32, 200, 1), (12, 32, 929, 0),
+                                                  (12, 36, 257, 0), (12, 37, 929, 1), (12, 48, 929, 1)])
+def test_instances_of_a_few_requests(sl, orc, inst, n, chains, before):
+    import torch
+    rng = np.random.default_rng(n + chains)
+    q = random_queue(rng, n, max_in=100, max_out=20, thr_hi=40_000 * n)
+    where = (np.arange(n) % inst).astype(np.int32)
+    dq, dw = sl.DeviceQueue.from_queue(q), torch.from_numpy(where).cuda()
+
+    def selected(mws):
+        status = sl.sched_multi_status(mws).cpu().tolist()
+        assert status[0] == 0, status
+        return status[2]
+    wide = dict(COEF, d2=1 << 25)
+    assert selected(sl.sched_anneal_multi(dq, Model(2, 1, t_ref_us=1, **wide), dw, inst, chains, 1, 0.7, 0.99, 3)) == before
+    m = Model(2, 1, **COEF)
+    mws = sl.sched_anneal_multi(dq, m, dw, inst, chains, 40, 0.7, 0.99, 3)
+    assert selected(mws) == 0
+    for k in (0, inst - 1):
+        ids = np.flatnonzero(where == k)
+        sub = Queue(q.in_len[ids], q.out_len[ids], q.kind[ids], q.thr_us[ids])
+        rec = sl.sched_chains(mws.instance(k), len(ids), chains).cpu().numpy()
+        info = orc.start(sub, m)
+        for c in (0, chains // 2, chains - 1):
+            assert np.array_equal(rec[c], orc.anneal_chain(sub, m, k * chains + c, 40, 0.7, 0.99, 3, start_info=info)["rec"]), (k, c)
