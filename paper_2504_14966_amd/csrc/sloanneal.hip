@@ -1157,7 +1157,7 @@ int sched_anneal_fit(const sched_queue_t *queue, const sched_fit_model_t *fit, c
     // times sum to below 2^38 and the kernel above runs: listing this one too added a launch that
     // returned at once, 4 us of 60)
     const size_t soa = (size_t)n * 16, per = sa::fit_chain_bytes(n);
-    const int waves = sa::lds_shape(chains, soa, per, max_lds_per_block(), cu_count()).waves;
+    const int waves = sa::lds_shape_small(chains, soa, per, max_lds_per_block(), cu_count()).waves;
     if (waves > 0) {
       const size_t lds = soa + per * waves;
       const int grid = (chains + waves - 1) / waves;

@@ -140,3 +140,22 @@ def test_instances_of_a_few_requests(sl, orc, inst, n, chains, before):
         info = orc.start(sub, m)
         for c in (0, chains // 2, chains - 1):
             assert np.array_equal(rec[c], orc.anneal_chain(sub, m, k * chains + c, 40, 0.7, 0.99, 3, start_info=info)["rec"]), (k, c)
+
+
+@pytest.mark.parametrize("n,B,chains", [(70, 3, 4099), (300, 16, 5002), (1000, 8, 4201)])
+@pytest.mark.parametrize("policy", [0, 2])
+def test_fitted_chains_beyond_one_workgroup_per_cu(sl, orc, n, B, chains, policy):
+    # workgroups of four with a ragged last one, and (1000 requests) of nine
+    rng = np.random.default_rng(n + policy)
+    q = random_queue(rng, n, max_in=2000, max_out=100, thr_hi=40_000_000)
+    coef = dict(ap=3, bp=500, cp=20, dp=4000, ad=1, bd=70, cd=5, dd=9000)
+    fd, fo = sl.FitModel(B, policy, **coef), orc.FitModel(B, policy, **coef)
+    ws = sl.sched_anneal_fit(sl.DeviceQueue.from_queue(q), fd, chains, 60, 0.7, 0.99, 3)
+    assert _selected(sl, ws) == 0
+    rec, cur, best = sl.sched_chains(ws, n, chains, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    info = orc.start_fit(q, fo)
+    for c in (0, 3, 4, chains // 2, chains - 2, chains - 1):
+        w = orc.anneal_chain_fit(q, fo, c, 60, 0.7, 0.99, 3, start_info=info)
+        assert np.array_equal(rec[c], w["rec"]), c
+        assert np.array_equal(cur[c], w["cur"]) and np.array_equal(best[c], w["best"]), c

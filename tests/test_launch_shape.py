@@ -17,6 +17,7 @@ extern "C" void shapes(long k, const int *chains, const long *shared, const long
     out[3 * i] = s.fit;
     out[3 * i + 1] = s.waves;
     out[3 * i + 2] = sa::lds_suffices(s, chains[i], cus);
+    out[3 * i + 2] |= sa::lds_shape_small(chains[i], (size_t)shared[i], (size_t)per[i], lim, cus).waves << 8;
   }
 }
 """
@@ -30,12 +31,13 @@ def shapes(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", so], check=True)
     lib = C.CDLL(so)
 
-    def call(chains, shared, per):
+    def call(chains, shared, per, small=False):
         chains, shared, per = np.broadcast_arrays(chains, shared, per)
         c, s, p = (np.ascontiguousarray(a, t) for a, t in ((chains, np.int32), (shared, np.int64), (per, np.int64)))
         out = np.zeros((c.size, 3), np.int32)
         lib.shapes(C.c_long(c.size), c.ctypes, s.ctypes, p.ctypes, LIM, CUS, out.ctypes)
-        return tuple(out.reshape(c.shape + (3,)).transpose(-1, *range(c.ndim)))
+        fit, waves, rest = out.reshape(c.shape + (3,)).transpose(-1, *range(c.ndim))
+        return (fit, waves, rest & 255) + ((rest >> 8,) if small else ())
     return call
 
 
@@ -114,3 +116,17 @@ def test_eval_workgroups_of_measured_calls(eval_grid):
     assert eval_grid(32768, 4, 14144, 7, 2.5) == 1792  # layouts, 400 requests: 2048 took 1.4 times as long
     assert eval_grid(32768, 4, 1500, 8, 1.5) == 2048   # 10 requests: 8192 took twice as long
     assert eval_grid(1 << 20, 4, 8000, 8, 1.5) == 8192
+
+
+def test_fitted_chains_beyond_one_workgroup_per_cu(shapes):
+    """Blocks of 28 bytes per request and a fixed part: beyond 16 chains per CU the workgroups are of
+    four, one chain per SIMD, while the LDS holds five of them; up to there the spread of the others."""
+    n = np.arange(65, 1025, 13)[:, None]
+    chains = np.concatenate([np.arange(1, 4097, 61), [4096], np.arange(4097, 20000, 307)])[None, :]
+    per = (2 * n + 15) // 16 * 16 + (n + 15) // 16 * 16 + 1440
+    fit, waves, _, small = shapes(chains, 16 * n, per, small=True)
+    nn, cc, pp = np.broadcast_arrays(n, chains, per)
+    packed = (cc > 16 * CUS) & (5 * (16 * nn + 4 * pp) <= LIM)
+    assert (fit == 16).all() and packed.any() and (packed != (cc > 16 * CUS)).any()
+    assert (small[packed] == 4).all() and (small[~packed] == waves[~packed]).all()
+    assert shapes(5000, 16 * 256, 2208, small=True)[3] == 4
