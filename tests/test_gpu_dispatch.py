@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(__file__))
-from gpu_helpers import oracle_chains  # noqa: E402
+from gpu_helpers import oracle_chains, oracle_chains_batches  # noqa: E402
 
 from paper_2504_14966_amd.workloads import Model, Queue, random_queue  # noqa: E402
 
@@ -159,3 +159,53 @@ def test_fitted_chains_beyond_one_workgroup_per_cu(sl, orc, n, B, chains, policy
         w = orc.anneal_chain_fit(q, fo, c, 60, 0.7, 0.99, 3, start_info=info)
         assert np.array_equal(rec[c], w["rec"]), c
         assert np.array_equal(cur[c], w["cur"]) and np.array_equal(best[c], w["best"]), c
+
+
+# Uneven workgroups: 3, 5, 6 and 7 chains each (as many as spread the chains over 256 CUs) and a
+# ragged last one. (requests, batch, policy, coefficients, kernel that runs): the limit rows and the
+# delta kernel of fixed-size batches, the batch-size search and list scheduling with one wave per
+# chain (a timeline beyond 32 bits, where the kernel listed first does not run)
+UNEVEN = {"limit_rows": (200, 20, 0, COEF, 0), "delta": (200, 3, 0, COEF, 0), "wave": (200, 40, 0, dict(COEF, d0=8_000_000), 1),
+          "search": (100, 9, 2, COEF, 0), "list": (60, 7, 1, dict(COEF, d0=8_000_000), 1)}
+
+
+@pytest.mark.parametrize("name", sorted(UNEVEN))
+@pytest.mark.parametrize("chains", [601, 1201, 1501, 1700])
+def test_uneven_workgroups(sl, orc, name, chains):
+    n, B, policy, coef, selected = UNEVEN[name]
+    rng = np.random.default_rng(chains + n)
+    q = random_queue(rng, n, max_in=400, max_out=60, thr_hi=40_000 * n)
+    m, iters = Model(B, policy, **coef), 50
+    ws = sl.sched_anneal(sl.DeviceQueue.from_queue(q), m, chains, iters, 0.7, 0.99, 5)
+    assert _selected(sl, ws) == selected
+    waves = -(-chains // 256)
+    sample = sorted({0, waves - 1, waves, chains // 2, chains // waves * waves - 1, chains - 1})
+    rec, cur, best = sl.sched_chains(ws, n, chains, perms=True)
+    rec, cur, best = rec.cpu().numpy(), sl.as_u16(cur), sl.as_u16(best)
+    info = orc.start(q, m)
+    if policy == 2:
+        cs, bs, _ = sl.sched_starts(ws, n, chains)
+        cs, bs = cs.cpu().numpy(), bs.cpu().numpy()
+        for c, w in oracle_chains_batches(q, m, sample, iters, 0.7, 0.99, 5, info).items():
+            assert np.array_equal(rec[c], w["rec"]), c
+            assert np.array_equal(cur[c], w["cur"]) and np.array_equal(best[c], w["best"]), c
+            assert np.array_equal(cs[c], w["cur_starts"]) and np.array_equal(bs[c], w["best_starts"]), c
+        return
+    for c, (r, cu, be) in oracle_chains(q, m, sample, iters, 0.7, 0.99, 5, info).items():
+        assert np.array_equal(rec[c], r), c
+        assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
+
+
+@pytest.mark.parametrize("chains", [601, 1201, 1501, 1700])
+def test_uneven_workgroups_fitted(sl, orc, chains):
+    rng = np.random.default_rng(chains)
+    n, iters, waves = 150, 60, -(-chains // 256)
+    q = random_queue(rng, n, max_in=2000, max_out=100, thr_hi=40_000_000)
+    coef = dict(ap=3, bp=500, cp=20, dp=4000, ad=1, bd=70, cd=5, dd=9000)
+    fd, fo = sl.FitModel(6, 2, **coef), orc.FitModel(6, 2, **coef)
+    ws = sl.sched_anneal_fit(sl.DeviceQueue.from_queue(q), fd, chains, iters, 0.7, 0.99, 5)
+    assert _selected(sl, ws) == 0
+    rec = sl.sched_chains(ws, n, chains).cpu().numpy()
+    info = orc.start_fit(q, fo)
+    for c in (0, waves - 1, waves, chains // 2, chains // waves * waves - 1, chains - 1):
+        assert np.array_equal(rec[c], orc.anneal_chain_fit(q, fo, c, iters, 0.7, 0.99, 5, start_info=info)["rec"]), c
