@@ -26,6 +26,7 @@
 #include "device_rng.h"
 #include "anneal_static.h"
 #include "kernels.h"
+#include "lane_shape.h"
 
 namespace sa {
 
@@ -314,12 +315,6 @@ __device__ __forceinline__ Score replay_batches(const DevModel &m, const uint4 *
     return replay_batches_windows32<DETAIL>(m, req, perm, flags, stage, detail);
   if (m.flags & kFlagWindows) return replay_batches_windows<DETAIL>(m, req, perm, flags, stage, detail);
   return replay_batches_one<DETAIL>(m, req, perm, flags, stage, detail);
-}
-
-// LDS one wave needs to validate and replay one (order, layout) row: order, flags, the
-// replay's staging and the validity bitmap.
-__host__ __device__ __forceinline__ size_t sized_row_bytes(int n) {
-  return (((size_t)n * 2 + 15) & ~size_t(15)) + (((size_t)n + 15) & ~size_t(15)) + 64 * 16 + 32 * 4;
 }
 
 // One (order, layout) row by one wave: validated ((-1, -1) otherwise), then replayed.

@@ -26,16 +26,9 @@
 // 230 us, one order per wave 1642 us).
 #pragma once
 #include "anneal_static.h"
+#include "lane_shape.h"
 
 namespace sa {
-
-constexpr int kContStage = 32;               // positions staged at a time
-constexpr int kContIdStride = kContStage + 2;  // u16 entries per lane
-
-// LDS of one wave: slots (8 B), staged ids and the bitmap, per lane.
-__host__ __device__ __forceinline__ size_t cont_lane_wave_bytes(int n, int cap) {
-  return (size_t)kWave * (cap * 8 + kContIdStride * 2 + ((n + 31) / 32) * 4);
-}
 
 __device__ __forceinline__ uint32_t med3_v(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t d;

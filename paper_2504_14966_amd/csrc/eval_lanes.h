@@ -38,25 +38,11 @@
 #include <type_traits>
 
 #include "anneal_sized.h"
+#include "lane_shape.h"
 
 namespace sa {
 
-constexpr int kLaneInvStride = kWave + 4;  // bytes per request: 64 orders, padded across the banks
-constexpr int kLaneDepth = 8;              // requests whose LDS accesses are in flight together
-
-__host__ __device__ __forceinline__ size_t lane_inv_bytes(int n) {
-  return round_up((size_t)(n + 1) * kLaneInvStride, 16);  // a spare row takes ids out of range
-}
-__host__ __device__ __forceinline__ int lane_words(int n) { return ((n + 31) / 32) | 1; }
-// LDS shared by a workgroup: the three sorted tables, and the requests by id for layouts.
-__host__ __device__ __forceinline__ size_t lane_shared_bytes(int n, bool layout) { return (size_t)n * (layout ? 64 : 48); }
-// LDS of one wave: inv, the entries (U, W) and T0 of mcap batches and a spare, and for
-// layouts the start bits with their running counts and the rows' flags.
-__host__ __device__ __forceinline__ size_t lane_wave_bytes(int n, int mcap, bool layout) {
-  const size_t own = lane_inv_bytes(n) + (size_t)(mcap + 1) * (kWave * 12) +
-                     (layout ? (size_t)kWave * lane_words(n) * 8 + kWave * 4 : 0);
-  return layout && own < sized_row_bytes(n) ? sized_row_bytes(n) : own;
-}
+constexpr int kLaneDepth = 8;  // requests whose LDS accesses are in flight together
 
 // Start bits of the tile's layouts, their running counts per 32-position word, and the number
 // of batches of the lane's row (0: not a valid layout).

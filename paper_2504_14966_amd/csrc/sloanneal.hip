@@ -92,17 +92,6 @@ constexpr uint32_t kAnnealFlags = sa::kFlagNarrowPrefill | sa::kFlagListSched | 
 constexpr uint32_t kEvalFlags = sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime;
 constexpr uint32_t kMultiFlags = kEvalFlags;
 constexpr uint32_t kSN = sa::kFlagStaticNarrow, kT32 = sa::kFlagTime32;
-// Rows from which evaluation runs with one order per lane: a tile of 64 orders then takes a
-// wave about as long as the one-order-per-wave kernels take for all rows, and every SIMD has
-// one. Measured crossings (us, lanes against waves): static, 128 requests, batches of 16: 33
-// against 34 at 32768 rows, 35 against 51 at 65536, but batches of 4 only 37 against 41 at
-// 65536 (38 against 32 at 32768); layouts, the same queue: 39 against 52 at 16384; continuous,
-// 32 running: 58 against 43 at 16384 rows of 128 requests and 58 against 82 at 32768, while
-// with long queues the scans' LDS leaves the other kernel few waves (1024 requests: 1.8 times
-// its rate at 8192 rows) and short ones are over in a few events.
-int64_t eval_lane_rows(int n, int B, bool layout) { return layout ? 16384 : (n <= 64 || B >= 16 ? 32768 : 65536); }
-int64_t eval_cont_lane_rows(int n) { return n >= 768 ? 8192 : (n >= 320 || n <= 24 ? 16384 : 32768); }
-
 // The kernels one call may run, in order of preference, each with the width flags it needs
 // and the ones it may use. All of them are enqueued; on the device each reads the verdict of
 // the checks and only the first whose needs hold runs (the last needs none, so exactly one
@@ -731,61 +720,50 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
   });
 }
 
-// Static evaluation with one order per lane, for enough rows to give every SIMD a wave and
-// short enough queues for the LDS to hold four waves per CU.
+// Static evaluation with one order per lane.
 template <bool LAYOUT>
 void add_eval_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
                     const uint16_t *perms, const uint8_t *starts, int64_t k, int64_t *out, const Limits &dl,
                     hipStream_t stream) {
-  const int cus = dl.cus, lim = dl.lds - (int)sa::kCheckLdsBytes;
-  if (n < 2 || k < eval_lane_rows(n, model->max_batch, LAYOUT)) return;
+  const int lim = dl.lds - (int)sa::kCheckLdsBytes;
+  const sa::LaneShape s = sa::eval_lane_shape(n, model->max_batch, LAYOUT, k, lim);
+  if (s.waves == 0) return;
   // the tile's ids and flags are read 16 bytes at a time (a tile of 64 rows keeps the alignment)
   if ((reinterpret_cast<uintptr_t>(perms) | reinterpret_cast<uintptr_t>(starts)) & 15u) return;
-  const int M = (n + model->max_batch - 1) / model->max_batch;
-  const int mcap = LAYOUT ? std::min(n, 3 * M + 4) : M;
-  const size_t shared = sa::lane_shared_bytes(n, LAYOUT), per = sa::lane_wave_bytes(n, mcap, LAYOUT);
-  if (mcap > 254 || shared + 4 * per > (size_t)lim) return;
-  const size_t lds = shared + 4 * per;
-  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / lds)));
-  const int grid = (int)std::min<int64_t>((k + 255) / 256, (int64_t)cus * per_cu);
+  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / s.lds)));
+  const int grid = (int)std::min<int64_t>((k + 255) / 256, (int64_t)dl.cus * per_cu);
   c.add(kSN | kT32 | sa::kFlagEvalLaneSums, kEvalFlags | sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {
     const void *fn = (const void *)&sa::eval_lanes_kernel<LAYOUT>;
-    if (lds > 65536) {
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (s.lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
       if (e != hipSuccess) return e;
     }
-    sa::eval_lanes_kernel<LAYOUT><<<grid, 256, lds, stream>>>(d, qp, perms, starts, k, out, mcap);
+    sa::eval_lanes_kernel<LAYOUT><<<grid, 256, s.lds, stream>>>(d, qp, perms, starts, k, out, s.cap);
     return hipGetLastError();
   });
 }
 
-// Continuous evaluation with one order per lane (the list holds the running requests in 8, 16,
-// 32 or 64 registers), for enough rows to give every SIMD a wave.
+// Continuous evaluation with one order per lane.
 void add_eval_cont_lanes(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const sa::QueuePtrs &qp,
                          const uint16_t *perms, int64_t k, int64_t *out, const Limits &dl, hipStream_t stream) {
-  const int cus = dl.cus, lim = dl.lds - (int)sa::kCheckLdsBytes;
-  if (k < eval_cont_lane_rows(n)) return;
-  const int n0 = std::min(model->max_batch, n), cap = n0 <= 8 ? 8 : (n0 <= 16 ? 16 : (n0 <= 32 ? 32 : 64));
-  const size_t shared = (size_t)n * 16, per = sa::cont_lane_wave_bytes(n, cap);
-  int waves = 4;
-  while (waves > 1 && shared + waves * per > (size_t)lim) --waves;
-  const size_t lds = shared + waves * per;
-  if (lds > (size_t)lim) return;
-  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / lds)));
+  const int lim = dl.lds - (int)sa::kCheckLdsBytes;
+  const sa::LaneShape s = sa::eval_cont_lane_shape(n, model->max_batch, k, lim);
+  if (s.waves == 0) return;
+  const int per_cu = std::max(1, std::min(8, (int)((size_t)lim / s.lds)));
   const int64_t tiles = (k + 63) / 64;
-  const int grid = (int)std::min<int64_t>((tiles + waves - 1) / waves, (int64_t)cus * per_cu);
+  const int grid = (int)std::min<int64_t>((tiles + s.waves - 1) / s.waves, (int64_t)dl.cus * per_cu);
   c.add(sa::kFlagNarrowPrefill | sa::kFlagListSched | sa::kFlagNarrowTime | sa::kFlagEvalLaneCont, kEvalFlags,
         [=](const sa::DevModel &d) {
           auto go = [&](auto kernel) {
-            if (lds > 65536) {
+            if (s.lds > 65536) {
               const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
               if (e != hipSuccess) return e;
             }
-            kernel<<<grid, waves * 64, lds, stream>>>(d, qp, perms, k, out);
+            kernel<<<grid, s.waves * 64, s.lds, stream>>>(d, qp, perms, k, out);
             return hipGetLastError();
           };
-          switch (cap) {
+          switch (s.cap) {
             case 8: return go(&sa::eval_cont_lanes_kernel<8>);
             case 16: return go(&sa::eval_cont_lanes_kernel<16>);
             case 32: return go(&sa::eval_cont_lanes_kernel<32>);

@@ -6,6 +6,45 @@ import os
 import numpy as np
 
 
+_LANE_SHIM = r"""
+#define __host__
+#define __device__
+#define __forceinline__ inline
+#include "lane_shape.h"
+extern "C" void shape(int n, int B, int kind, long rows, int lim, long *out) {
+  const sa::LaneShape s =
+      kind == 2 ? sa::eval_cont_lane_shape(n, B, rows, lim) : sa::eval_lane_shape(n, B, kind == 1, rows, lim);
+  out[0] = s.waves;
+  out[1] = (long)s.lds;
+  out[2] = s.cap;
+}
+"""
+_lane_lib = None
+
+
+def lane_shape(kind: str, n: int, B: int, rows: int):
+    """(waves per workgroup, LDS, batches or registers per lane) of the one-order-per-lane evaluation
+    kernel, from the dispatch's own header; waves is 0 where a call does not take it. kind: static,
+    layout or continuous."""
+    global _lane_lib
+    import ctypes as C
+    import subprocess
+    import tempfile
+    if _lane_lib is None:
+        csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_14966_amd", "csrc")
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+            with open(src, "w") as f:
+                f.write(_LANE_SHIM)
+            subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", csrc, src, "-o", so], check=True)
+            _lane_lib = C.CDLL(so)
+        _lane_lib.shape.argtypes = [C.c_int, C.c_int, C.c_int, C.c_long, C.c_int, C.c_void_p]
+    out = (C.c_long * 3)()
+    # 160 KB of LDS less what the checks take
+    _lane_lib.shape(n, B, ("static", "layout", "continuous").index(kind), rows, 160 * 1024 - 1024, out)
+    return tuple(out)
+
+
 def _search(search):
     import oracle
     return None if search is None else oracle.Search(*search)

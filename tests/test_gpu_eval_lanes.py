@@ -1,8 +1,9 @@
 """Evaluation paths that depend on the number of rows, against the oracle (bit-exact).
 
 Candidate launches: a call whose first candidate is not the one selected, with more rows than
-one pass of the grid. One order per lane: row counts that reach those kernels, every row against
-the one-order-per-wave kernels (reached by calls of few rows) and a sample against the oracle.
+one pass of the grid. One order per lane: row counts that reach those kernels (checked against the
+dispatch's own rule), every row against the one-order-per-wave kernels (reached by calls of few
+rows) and a sample against the oracle.
 """
 import os
 import sys
@@ -11,7 +12,7 @@ import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.dirname(__file__))
-from gpu_helpers import oracle_rows  # noqa: E402
+from gpu_helpers import lane_shape, oracle_rows  # noqa: E402
 
 from paper_2504_14966_amd.workloads import Model, random_queue  # noqa: E402
 
@@ -69,13 +70,14 @@ def _layouts(rng, k, n, B):
 
 
 # (n, B): one to many batches per lane, rows that straddle the 16-byte chunks of ids and flags,
-# 32-position words with a remainder, the largest that fits, and batches of the whole queue
+# 32-position words with a remainder, and batches of the whole queue
 LANES = [(2, 1), (7, 3), (10, 4), (16, 16), (33, 8), (64, 64), (100, 24), (128, 16), (200, 64)]
 
 
-@pytest.mark.parametrize("n,B", LANES)
+@pytest.mark.parametrize("n,B", LANES + [(431, 64)])  # the longest queue that fits
 @pytest.mark.parametrize("rows", [65536, 65536 + 77])
 def test_static_lanes(sl, orc, n, B, rows):
+    assert lane_shape("static", n, B, rows)[0] == 4 and lane_shape("static", n, B, 8192)[0] == 0
     rng = np.random.default_rng(1000 * n + B + rows)
     q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
     m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2)
@@ -92,10 +94,14 @@ def test_static_lanes(sl, orc, n, B, rows):
     assert np.array_equal(got[some], orc.eval_rows(q, m, p[some]))
 
 
-@pytest.mark.parametrize("n,B", LANES + [(40, 2), (300, 64)])
+@pytest.mark.parametrize("n,B", LANES + [(40, 2), (256, 64)])  # the last one the longest that fits
 @pytest.mark.parametrize("rows", [16384, 16384 + 77])
 def test_layout_lanes(sl, orc, n, B, rows):
-    # (40, 2): some valid layouts have more batches than a lane's entries hold
+    waves, _, cap = lane_shape("layout", n, B, rows)
+    assert waves == 4 and lane_shape("layout", n, B, 8192)[0] == 0
+    # the layouts of single requests below have more batches than a lane's entries hold, but where
+    # those hold one per request
+    assert (cap < n) == ((n, B) in [(33, 8), (64, 64), (100, 24), (128, 16), (200, 64), (256, 64), (16, 16)])
     rng = np.random.default_rng(1000 * n + B + rows + 1)
     q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
     m = Model(B, 2, p0=2000, p1=40, d0=8000, d1=300, d2=2)
@@ -134,6 +140,7 @@ def test_static_lanes_widths(sl, orc, field, value):
     # both sides of the 24-bit factors: a full batch's sum of d1, and d2 L (L + 1) / 2 with d2 = 1
     rng = np.random.default_rng(value)
     n, B, rows = 24, 16, 32768
+    assert lane_shape("static", n, B, rows)[0] == 4
     q = random_queue(rng, n, max_in=60, max_out=15, thr_hi=1_000_000_000)
     m = Model(B, 0, p0=10, p1=1, d0=10, d1=300, d2=0)
     if field == "d1":
@@ -153,6 +160,7 @@ def test_lanes_unaligned_rows(sl, orc):
     import torch
     rng = np.random.default_rng(3)
     n, B, rows = 10, 4, 40_000
+    assert lane_shape("static", n, B, rows)[0] == 4 and lane_shape("layout", n, B, rows)[0] == 4
     q = random_queue(rng, n, max_in=2048, max_out=400, thr_hi=5_000_000)
     m = Model(B, 0, p0=2000, p1=40, d0=8000, d1=300, d2=2)
     p, s = _orders(rng, rows + 1, n), _layouts(rng, rows + 1, n, B)
@@ -178,6 +186,7 @@ def test_continuous_lanes(sl, orc, n, B, ties):
     # the prefills at hand), with thresholds where TTFT, TPOT and end-to-end flags are mixed
     rng = np.random.default_rng(1000 * n + B + ties)
     rows = 32768 + 77
+    assert lane_shape("continuous", n, B, rows)[0] > 0 and lane_shape("continuous", n, B, 4096)[0] == 0
     q = random_queue(rng, n, max_in=2048, max_out=3 if ties else 400, thr_hi=200_000 if ties else 5_000_000)
     m = Model(B, 1, p0=2000, p1=40, d0=8000, d1=300, d2=2)
     p = _orders(rng, rows, n)
@@ -198,6 +207,7 @@ def test_continuous_lanes_widths(sl, orc, field, value):
     # both sides of the 24-bit factors; the largest threshold; a model whose every time is zero
     rng = np.random.default_rng(value + 5)
     n, B, rows = 20, 6, 16384
+    assert lane_shape("continuous", n, B, rows)[0] > 0
     q = random_queue(rng, n, max_in=9, max_out=6, thr_hi=100_000_000)
     m = Model(B, 1, p0=10, p1=1, d0=10, d1=3, d2=1)
     if field == "out":

@@ -2,9 +2,13 @@
 import ctypes as C
 import os
 import subprocess
+import sys
 
 import numpy as np
 import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+from gpu_helpers import lane_shape  # noqa: E402
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_14966_amd", "csrc")
 LIM, CUS = 160 * 1024, 256
@@ -130,3 +134,26 @@ def test_fitted_chains_beyond_one_workgroup_per_cu(shapes):
     assert (fit == 16).all() and packed.any() and (packed != (cc > 16 * CUS)).any()
     assert (small[packed] == 4).all() and (small[~packed] == waves[~packed]).all()
     assert shapes(5000, 16 * 256, 2208, small=True)[3] == 4
+
+
+@pytest.mark.parametrize("kind,B,longest", [("static", 1, 47), ("static", 4, 144), ("static", 16, 306), ("static", 64, 431),
+                                            ("layout", 4, 52), ("layout", 8, 88), ("layout", 16, 144), ("layout", 32, 200),
+                                            ("layout", 64, 256)])
+def test_longest_queues_of_the_lane_kernels(kind, B, longest):
+    """Four waves per workgroup or none: where the LDS ends. (300 requests by layout go to the
+    one-order-per-wave kernel at any row count.)"""
+    rows = 1 << 20
+    taken = [n for n in range(2, 1025) if lane_shape(kind, n, B, rows)[0]]
+    assert taken[-1] == longest and taken == list(range(2, longest + 1))
+    assert lane_shape("layout", 300, 64, rows)[0] == 0
+    waves, lds, cap = lane_shape(kind, longest, B, rows)
+    assert waves == 4 and lds <= LIM - 1024 and cap >= -(-longest // B)
+
+
+def test_continuous_lane_kernel_steps_its_waves_down():
+    rows = 1 << 20
+    got = {(n, B): lane_shape("continuous", n, B, rows) for n in (2, 24, 256, 1024) for B in (1, 9, 32, 64)}
+    assert all(w > 0 and lds <= LIM - 1024 for w, lds, _ in got.values())
+    assert got[(1024, 64)][0] < got[(256, 32)][0] == 4
+    assert [got[(1024, B)][2] for B in (1, 9, 32, 64)] == [8, 16, 32, 64]
+    assert lane_shape("continuous", 256, 32, 32767)[0] == 0 and lane_shape("continuous", 1024, 32, 8192)[0] > 0
