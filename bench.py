@@ -131,7 +131,7 @@ def expected_work(W) -> dict:
 # one such workgroup per CU, the registers five waves per SIMD).
 HEADLINE_KERNEL_SOURCES = ("anneal_wave_rows.h", "anneal_wave.h", "anneal_sized.h", "anneal_static.h", "kernels.h",
                            "device_cont.h", "device_plan.h", "device_replay.h", "device_rng.h", "device_common.h",
-                           "sloanneal.hip")
+                           "launch_shape.h", "lane_shape.h", "sloanneal.hip")
 PROFILE_BY_SOURCE = {
     # anneal_rows_kernel<0, 16> on the burst workload: 17,423,168 B of HBM traffic (FETCH_SIZE
     # x 2.0 + WRITE_SIZE x 1.0); 441.7 VALU and 54.9 LDS instructions, 116.3 bank-conflict

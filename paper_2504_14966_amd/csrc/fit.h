@@ -12,9 +12,11 @@
 // SLO kinds: the three single ones and kind 3, the paper's chat SLO (TTFT <= thr and TPOT
 // <= thr2, thr2 from a second per-request array).
 //
-// Batches are either of the maximum size or given by start flags (the batch-size search),
-// and every proposal is replayed in full, one batch at a time with the members in lanes:
-// per member one closed form, per batch a wave maximum. All arithmetic is 64-bit.
+// Batches are either of the maximum size or given by start flags (the batch-size search). A replay
+// takes windows of whole batches, one position per lane: per member one closed form, the batch
+// durations by one scan; chains whose member times fit 32 bits restart at the window of the first
+// change, the others replay in full. Times of 2^57 and more: one batch at a time, a wave maximum
+// each.
 #pragma once
 #include "anneal_sized.h"
 #include "anneal_wave.h"
@@ -188,14 +190,13 @@ __device__ Score replay_fit_windows(const DevFit &f, const uint4 *__restrict__ r
   return Score{nmet, wave_sum_u64(tl)};
 }
 
-// The same windows when every member's time fits 32 bits (totals only): the closed forms in
-// 32-bit arithmetic (exact, the wrap-around only inside ring expressions whose value fits),
+// The same windows when every member's time fits 32 bits, for the start order's totals (batches of
+// the maximum size): the closed forms in 32-bit arithmetic (exact, the wrap-around only inside ring expressions whose value fits),
 // durations by the 32-bit max-scan confined to batches, starts by saturating 32-bit scans
 // (a start that saturates meets no threshold, every threshold being below 2^32 - 1), and
 // the total latency exactly as the sum of the member times plus each batch's duration times
 // the number of requests after it.
-__device__ Score replay_fit_windows32(const DevFit &f, const uint4 *__restrict__ req, const uint16_t *perm,
-                                      const uint8_t *flags) {
+__device__ Score replay_fit_windows32(const DevFit &f, const uint4 *__restrict__ req, const uint16_t *perm) {
   const int lane = lane_id();
   const int n = f.n, B = f.B;
   const uint32_t ap = (uint32_t)f.ap, bp = (uint32_t)f.bp, cp = (uint32_t)f.cp, dp = (uint32_t)f.dp;
@@ -206,12 +207,9 @@ __device__ Score replay_fit_windows32(const DevFit &f, const uint4 *__restrict__
   for (int s = 0; s < n;) {
     const int p = s + lane;
     bool st = p == n;
-    if (p < n) {
-      if (flags) st = lane == 0 || flags[p] != 0;
-      else st = (uint64_t)lane == (((uint64_t)lane * f.bmagic) >> 32) * (uint64_t)B;
-    }
+    if (p < n) st = (uint64_t)lane == (((uint64_t)lane * f.bmagic) >> 32) * (uint64_t)B;
     bool st64 = s + kWave == n;
-    if (s + kWave < n) st64 = flags ? flags[s + kWave] != 0 : (kWave % B) == 0;
+    if (s + kWave < n) st64 = (kWave % B) == 0;
     uint64_t lastm = (__ballot(st) >> 1) | (st64 ? uint64_t(1) << 63 : 0ull);
     if (lastm == 0ull) lastm = uint64_t(1) << 63;
     const int w = 64 - __clzll(lastm);
@@ -377,7 +375,7 @@ __global__ void __launch_bounds__(1024) start_fit_kernel(DevFit f, QueuePtrs q, 
   }
   if (tid < 64) {
     auto score = [&](const uint16_t *order) {
-      return f.m32 ? replay_fit_windows32(f, req, order, nullptr) : replay_fit<false>(f, req, order, nullptr, nullptr);
+      return f.m32 ? replay_fit_windows32(f, req, order) : replay_fit<false>(f, req, order, nullptr, nullptr);
     };
     const Score sorted = score(key_id), input = score(ident);
     const bool input_better = srch.objective ? obj_better<1>(input.n, input.t, sorted.n, sorted.t)

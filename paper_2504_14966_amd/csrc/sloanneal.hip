@@ -348,9 +348,10 @@ bool stays_hot(const ChainArgs &a) { return lowest_temperature(a) >= 4.0; }
 // of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
 // other kernel's rows of two batches cost it more than twice a limit row (bounds, recounts):
 // 1500 chains of 389 requests in batches of 24 took 4.9 ms per 1000 proposals on it and 4.1 ms
-// here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2 against 2.4 (1024 chains of 256 requests) and 3.2
-// against 2.8 (4096 of 1000). With four batches in one of its rows it wins: 500 requests in
-// batches of 16: 2.2 against 2.9, in batches of 8 1.9 against 2.8.
+// here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2
+// against 2.4 (1024 chains of 256 requests) and 3.2 against 2.8 (4096 of 1000). With four batches
+// in one of its rows it wins: 500 requests in batches of 16: 2.2 against 2.9, in batches of 8 1.9
+// against 2.8.
 bool rows_pay(int n, int B) { return B >= 17 && (n + B - 1) / B <= 32; }
 
 template <int OBJ, int MR>
@@ -449,14 +450,15 @@ void add_cont_spec(Candidates<sa::DevModel> &c, const sched_model_t *model, int 
 }
 
 // The kernels a single-queue sched_anneal may run, by policy, in order of preference:
-//   static: the register kernel (up to 64 requests and batches up to 32; 65 to 192 with two or
-//     three positions per lane and batches of 1 .. 16, a power of two) or else the LDS delta kernel (one lane per
-//     batch member, or one batch per wave for batches of more than 32), both on the 32-bit
-//     pair-cost widths, the register kernel also on a 32-bit timeline when it holds, and
-//     one batch per wave with the members' SLO limits in registers ahead of the plain one
-//     when the timeline fits 32 bits;
-//   continuous: list scheduling when its 32-bit keys fit, the event loop when the 32-bit event
-//     arithmetic does, each as the LDS allows;
+//   static: for at most 16 requests whose chains stay hot, on a 32-bit timeline, the kernel that
+//     scores four proposals per round; the register kernel (up to 64 requests and batches up to 32,
+//     or any power of two up to 16; 65 to 192 requests with two or three positions per lane and
+//     batches of 1 .. 16, a power of two) or else the LDS delta kernels (one lane per batch member,
+//     or one batch per wave for batches of more than 32), both on the 32-bit pair-cost widths; ahead
+//     of the LDS delta kernels, for batches of 17 and more and at most 32 of them on a 32-bit
+//     timeline, one batch per wave with the members' SLO limits in registers;
+//   continuous: several proposals per round when every time fits 32 bits, list scheduling when its
+//     32-bit keys fit, the event loop when the 32-bit event arithmetic does, each as the LDS allows;
 //   always last: the full-replay kernel (any widths).
 template <int OBJ>
 void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, const ChainArgs &a) {
@@ -975,8 +977,8 @@ int sched_eval_batches(const sched_queue_t *queue, const sched_model_t *model, c
   const int grid = eval_workgroups(k, 4, lds, kEvalLayouts, dl);
   Candidates<sa::DevModel> c;
   if (!detail) add_eval_lanes<true>(c, model, n, qp, perms, starts, k, out, dl, stream);
-  // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are taken
-  // where they hold
+  // one order per wave: the windowed replay, the 32-bit pair costs and the 32-bit timeline are
+  // taken where they hold
   c.add(0u, sa::kFlagWindows | kSN | kT32, [=](const sa::DevModel &d) {
     if (detail)
       sa::eval_sized_kernel<true><<<grid, 256, lds, stream>>>(d, qp, perms, starts, k, out, detail);
