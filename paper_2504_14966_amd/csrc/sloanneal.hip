@@ -351,8 +351,9 @@ bool stays_hot(const ChainArgs &a) { return lowest_temperature(a) >= 4.0; }
 // here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2
 // against 2.4 (1024 chains of 256 requests) and 3.2 against 2.8 (4096 of 1000). With four batches
 // in one of its rows it wins: 500 requests in batches of 16: 2.2 against 2.9, in batches of 8 1.9
-// against 2.8.
-bool rows_pay(int n, int B) { return B >= 17 && (n + B - 1) / B <= 32; }
+// against 2.8. (One batch of up to 32 that holds every request needs no replay, and the limits of 8
+// rows only cost registers: 2000 chains of 2 to 30 requests took 6 % longer.)
+bool rows_pay(int n, int B) { return B >= 17 && (B > 32 || n > B) && (n + B - 1) / B <= 32; }
 
 template <int OBJ, int MR>
 hipError_t launch_rows(int waves, size_t lds, const sa::DevModel &d, const sa::StaticParams &sp, const ChainArgs &a) {

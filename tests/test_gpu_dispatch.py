@@ -209,3 +209,19 @@ def test_uneven_workgroups_fitted(sl, orc, chains):
     info = orc.start_fit(q, fo)
     for c in (0, waves - 1, waves, chains // 2, chains // waves * waves - 1, chains - 1):
         assert np.array_equal(rec[c], orc.anneal_chain_fit(q, fo, c, iters, 0.7, 0.99, 5, start_info=info)["rec"]), c
+
+
+# (requests, batch, candidates before the full replay): limit rows and the delta kernel; one batch of
+# up to 32 that holds every request leaves the limit rows out
+@pytest.mark.parametrize("n,B,before", [(2, 17, 1), (30, 32, 1), (32, 32, 1), (65, 32, 2), (66, 64, 2), (50, 64, 2)])
+def test_one_batch_takes_no_limit_rows(sl, orc, n, B, before):
+    rng = np.random.default_rng(n + B)
+    q = random_queue(rng, n, max_in=100, max_out=20, thr_hi=40_000 * n)
+    dq, chains = sl.DeviceQueue.from_queue(q), 2000
+    assert _selected(sl, sl.sched_anneal(dq, Model(B, 0, **WIDE), chains, 1, 0.7, 0.99, 3)) == before
+    m = Model(B, 0, **COEF)
+    ws = sl.sched_anneal(dq, m, chains, 60, 0.7, 0.99, 3)
+    assert _selected(sl, ws) == 0
+    rec = sl.sched_chains(ws, n, chains).cpu().numpy()
+    for c, (r, _, _) in oracle_chains(q, m, [0, 7, chains - 1], 60, 0.7, 0.99, 3, orc.start(q, m)).items():
+        assert np.array_equal(rec[c], r), c

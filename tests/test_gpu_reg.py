@@ -330,6 +330,7 @@ def test_hot_rows(sl, orc, n, B, thr, search, iters, T0):
 
 # the limit-row kernel below 33 per batch: the shortest batches it takes, ragged last batches of one
 # and of all but one, 32 batches (and 33, which it does not take), one batch holding everything
+# (20 of 20, 30 of 32: the delta kernel)
 @pytest.mark.parametrize("n,B", [(65, 17), (103, 17), (543, 17), (544, 17), (545, 17), (389, 24), (97, 32), (95, 32),
                                  (1024, 32), (20, 20), (30, 32), (200, 31),
                                  # 20, 21, 24, 25, 28 and 29 batches: the edges of the rows left out
