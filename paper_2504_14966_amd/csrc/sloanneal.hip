@@ -689,11 +689,11 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
       });
     }
   }
-  // Instances of two or three requests have little to replay, and many chains leave no issue slots
+  // Instances of two to three and a half requests have little to replay, and many chains leave no issue slots
   // for second proposals: the full replay by one wave per chain is faster there (12 instances of
-  // 3, 929 chains each: 0.80 of the time; of 2 from about 1024 chains in all: 0.63 to 0.9; of 4 it
-  // loses, 1.0 to 2.4).
-  const bool tiny = (n <= 2 * a.instances && total > 4 * cus) || (n <= 3 * a.instances && total > 12 * cus);
+  // 3, 929 chains each: 0.80 of the time; 10 of 3.2, 647 each: 0.91; of 2 from about 1024 chains in
+  // all: 0.63 to 0.9; of 4 it loses, 1.0 to 2.4).
+  const bool tiny = (n <= 2 * a.instances && total > 4 * cus) || (2 * n <= 7 * a.instances && total > 12 * cus);
   if (model->policy == SCHED_CONTINUOUS && !tiny) {
     // list scheduling, 32-bit times: LDS for instances of at most 64 or 192 requests, or of
     // the whole queue (more waves per chain when the chains leave the GPU nearly empty)

@@ -114,9 +114,9 @@ def test_two_proposals_per_round_by_chains(sl, orc, n, B, chains, before):
         assert np.array_equal(cur[c], cu) and np.array_equal(best[c], be), c
 
 
-# (instances, requests, chains, candidates before the full replay): mean sizes of 2, 3 and 4
+# (instances, requests, chains, candidates before the full replay): mean sizes of 2 to 4
 @pytest.mark.parametrize("inst,n,chains,before", [(4, 8, 256, 1), (4, 8, 257, 0), (12, 32, 200, 1), (12, 32, 929, 0),
-                                                  (12, 36, 257, 0), (12, 37, 929, 1), (12, 48, 929, 1)])
+                                                  (12, 36, 257, 0), (10, 35, 647, 0), (12, 43, 929, 1), (12, 48, 929, 1)])
 def test_instances_of_a_few_requests(sl, orc, inst, n, chains, before):
     import torch
     rng = np.random.default_rng(n + chains)
