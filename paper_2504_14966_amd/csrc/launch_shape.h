@@ -33,6 +33,14 @@ inline LdsShape lds_shape_small(int chains, size_t shared, size_t per, int lim, 
   return s;
 }
 
+// Chains per workgroup of the register kernels, at most four (one per SIMD): one while the chains are
+// at most two per CU, and beyond that as many as one workgroup per CU takes. Two workgroups of two
+// can share two SIMDs of a CU and leave the others idle: 600 to 1023 chains took 10 to 27 % longer
+// as twos, as long as 1024 do (64 requests in batches of 16: 323 against 276 us).
+inline int reg_shape(int chains, int cus) {
+  return chains > 2 * cus ? std::min(4, (chains + cus - 1) / cus) : 1;
+}
+
 // Whether the LDS gives the delta kernels of fixed-size batches enough chains at once: four per
 // CU (one per SIMD), or every chain in one pass. What counts is what the LDS holds, not the
 // spread: 1500 chains where five fit go as 500 workgroups of three.

@@ -239,12 +239,7 @@ size_t anneal_lds_bytes(int n) {
 // mean size decides: 3500 chains on instances of 6 in batches of 9, 494 against 443 us).
 bool reg_any_pays(int n, int B) { return B <= 32 && n > B; }
 
-// Chains per workgroup of the register kernels: four, or fewer so that the chains spread
-// over every CU.
-int reg_waves(int chains) {
-  const int cus = cu_count();
-  return chains >= 4 * cus ? 4 : (chains >= 2 * cus ? 2 : 1);
-}
+int reg_waves(int chains) { return sa::reg_shape(chains, cu_count()); }
 
 // Everything one sched_anneal launch needs besides the model and the gate.
 struct ChainArgs {
@@ -648,7 +643,7 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
   const int cus = cu_count();
   if (model->policy == SCHED_STATIC &&
       (sa::reg_form(B) != sa::kRegAny || reg_any_pays((n + a.instances - 1) / a.instances, B))) {
-    const int waves = total >= 4 * cus && a.chains >= 4 ? 4 : (total >= 2 * cus && a.chains >= 2 ? 2 : 1);
+    const int waves = std::min(sa::reg_shape(total, cus), a.chains);
     const int groups = (a.chains + waves - 1) / waves, grid = a.instances * groups;
     for (int parts = 0; parts <= (sa::reg_form(B) == sa::kRegAny ? 0 : 1); ++parts) {
       c.add(kSN | (parts ? sa::kFlagInst192 : sa::kFlagInst64), kMultiFlags | kT32, [=](const sa::DevModel &d) {

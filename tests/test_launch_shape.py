@@ -83,6 +83,7 @@ def test_delta_kernel_sizes_where_the_spread_is_three(shapes, n, B, chains):
 
 EVAL_SHIM = r"""
 #include "launch_shape.h"
+extern "C" int reg(int chains, int cus) { return sa::reg_shape(chains, cus); }
 extern "C" int grid(long rows, int waves, long lds, int per_simd, double beyond, int lim, int cus) {
   return sa::eval_grid(rows, waves, (size_t)lds, sa::EvalShape{per_simd, beyond}, lim, cus);
 }
@@ -97,7 +98,10 @@ def eval_grid(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"), "-o", so], check=True)
     lib = C.CDLL(so)
     lib.grid.argtypes = [C.c_long, C.c_int, C.c_long, C.c_int, C.c_double, C.c_int, C.c_int]
-    return lambda rows, waves, lds, per_simd, beyond: lib.grid(rows, waves, lds, per_simd, beyond, LIM, CUS)
+    def call(rows, waves, lds, per_simd, beyond):
+        return lib.grid(rows, waves, lds, per_simd, beyond, LIM, CUS)
+    call.reg = lib.reg
+    return call
 
 
 # (per SIMD, beyond, waves, LDS of a workgroup, held at once): the static, fitted, layout and any-width
@@ -157,3 +161,13 @@ def test_continuous_lane_kernel_steps_its_waves_down():
     assert got[(1024, 64)][0] < got[(256, 32)][0] == 4
     assert [got[(1024, B)][2] for B in (1, 9, 32, 64)] == [8, 16, 32, 64]
     assert lane_shape("continuous", 256, 32, 32767)[0] == 0 and lane_shape("continuous", 1024, 32, 8192)[0] > 0
+
+
+def test_register_kernels_put_one_chain_on_a_simd(eval_grid):
+    """From three chains per CU on, one workgroup per CU holds what it must: no two of them share SIMDs
+    while others idle. Up to two per CU one chain each."""
+    for chains in range(1, 6000):
+        w = eval_grid.reg(chains, CUS)
+        assert w == 1 if chains <= 2 * CUS else w in (3, 4), chains
+        assert chains <= 2 * CUS or w * CUS >= min(chains, 4 * CUS), chains
+        assert chains < 4 * CUS or w == 4, chains
