@@ -1,6 +1,5 @@
-// Workgroup shapes: the annealing kernels that keep a block of LDS per chain behind records shared
-// by the workgroup, and the one-order-per-wave evaluation kernels. Host arithmetic only, with no
-// HIP in it.
+// Workgroup shapes of the annealing kernels and of the one-order-per-wave evaluation kernels, and
+// which kernel of fixed-size batches pays. Host arithmetic only, with no HIP in it.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -47,6 +46,30 @@ inline int reg_shape(int chains, int cus) {
 inline bool lds_suffices(const LdsShape &s, int chains, int cus) {
   return s.fit >= 4 || (s.fit > 0 && (int64_t)s.fit * cus >= chains);
 }
+
+// Whether the register kernel's form for any batch size beats the LDS delta kernels: its cost
+// grows with the batch (two lane gathers per member: 64 requests in batches of 3 take 2.6 ms
+// against 6.0 ms, of 24 1.27 against 1.94 ms, of 33 1.31 against 1.27 ms), and when one batch
+// holds every request no proposal needs a replay and neither wins (with several instances the
+// mean size decides: 3500 chains on instances of 6 in batches of 9, 494 against 443 us). Two
+// batches of 17 to 32 are one row of the delta kernel, which issues less: it takes 0.87 to 0.99 of
+// the time while more than two waves share a SIMD and one pass holds every chain (`chains` 0: not
+// known), 1.1 to 1.25 of it below and 0.9 to 1.25 beyond.
+inline bool reg_any_pays(int n, int B, int chains = 0, int cus = 1) {
+  if (B >= 17 && n <= 2 * B && chains > 8 * cus && chains <= 16 * cus) return false;
+  return B <= 32 && n > B;
+}
+
+// One batch per wave with limit rows (timelines of 32 bits): batches of 17 and more, at most 32
+// of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
+// other kernel's rows of two batches cost it more than twice a limit row (bounds, recounts):
+// 1500 chains of 389 requests in batches of 24 took 4.9 ms per 1000 proposals on it and 4.1 ms
+// here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2
+// against 2.4 (1024 chains of 256 requests) and 3.2 against 2.8 (4096 of 1000). With four batches
+// in one of its rows it wins: 500 requests in batches of 16: 2.2 against 2.9, in batches of 8 1.9
+// against 2.8. (One or two batches of up to 32 are one of its rows: nothing to replay, 6 % longer
+// with limit rows at 2000 chains of 2 to 30 requests, or the case above.)
+inline bool rows_pay(int n, int B) { return B >= 17 && (B > 32 || n > 2 * B) && (n + B - 1) / B <= 32; }
 
 // Workgroups of a one-order-per-wave evaluation. Each forms the verdict and stages the requests
 // first, about 3 us, so no more than `held`, what the GPU holds at once, with every wave taking

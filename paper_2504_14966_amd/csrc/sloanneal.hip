@@ -232,13 +232,6 @@ size_t anneal_lds_bytes(int n) {
   return ((size_t)n * 16 + 15) / 16 * 16 + per_wave * sa::kWavesPerBlock;
 }
 
-// Whether the register kernel's form for any batch size beats the LDS delta kernels: its cost
-// grows with the batch (two lane gathers per member: 64 requests in batches of 3 take 2.6 ms
-// against 6.0 ms, of 24 1.27 against 1.94 ms, of 33 1.31 against 1.27 ms), and when one batch
-// holds every request no proposal needs a replay and neither wins (with several instances the
-// mean size decides: 3500 chains on instances of 6 in batches of 9, 494 against 443 us).
-bool reg_any_pays(int n, int B) { return B <= 32 && n > B; }
-
 int reg_waves(int chains) { return sa::reg_shape(chains, cu_count()); }
 
 // Everything one sched_anneal launch needs besides the model and the gate.
@@ -338,17 +331,6 @@ double lowest_temperature(const ChainArgs &a) {
 // That holds on the queue's own scale; with a t_ref of the caller's the device decides
 // (kFlagHotScale).
 bool stays_hot(const ChainArgs &a) { return lowest_temperature(a) >= 4.0; }
-
-// One batch per wave with limit rows (timelines of 32 bits): batches of 17 and more, at most 32
-// of them (the rows held in registers). Batches of 17 to 32 leave half the lanes idle, but the
-// other kernel's rows of two batches cost it more than twice a limit row (bounds, recounts):
-// 1500 chains of 389 requests in batches of 24 took 4.9 ms per 1000 proposals on it and 4.1 ms
-// here (3.5 ms with the rows past the last batch left out); batches of 17: 3.4 against 2.8; 32: 3.2
-// against 2.4 (1024 chains of 256 requests) and 3.2 against 2.8 (4096 of 1000). With four batches
-// in one of its rows it wins: 500 requests in batches of 16: 2.2 against 2.9, in batches of 8 1.9
-// against 2.8. (One batch of up to 32 that holds every request needs no replay, and the limits of 8
-// rows only cost registers: 2000 chains of 2 to 30 requests took 6 % longer.)
-bool rows_pay(int n, int B) { return B >= 17 && (B > 32 || n > B) && (n + B - 1) / B <= 32; }
 
 template <int OBJ, int MR>
 hipError_t launch_rows(int waves, size_t lds, const sa::DevModel &d, const sa::StaticParams &sp, const ChainArgs &a) {
@@ -482,7 +464,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
         }
       });
     }
-    if ((n <= 64 && (sa::reg_form(B) != sa::kRegAny || reg_any_pays(n, B))) || sa::reg_parts(n, B) > 1) {
+    if ((n <= 64 && (sa::reg_form(B) != sa::kRegAny || sa::reg_any_pays(n, B, a.chains, cu_count()))) || sa::reg_parts(n, B) > 1) {
       const bool parts = n > 64;
       const int waves = reg_waves(a.chains), grid = (a.chains + waves - 1) / waves;
       c.add(kSN, kAnnealFlags | kT32, [=](const sa::DevModel &d) {
@@ -506,7 +488,7 @@ void add_chains(Candidates<sa::DevModel> &c, const sched_model_t *model, int n, 
         const int waves = shape.waves;
         const sa::StaticParams sp{(uint32_t)model->d0, (uint32_t)model->d2, (1ull << 32) / (uint64_t)B + 1};
         const size_t lds = soa + per * waves;
-        if (rows_pay(n, B)) {
+        if (sa::rows_pay(n, B)) {
           // the limit-row kernel when the whole timeline fits 32 bits (its chains take a
           // little more LDS: the order carries 64 spare entries)
           const size_t rper = sa::rows_chain_bytes(n, B);
@@ -642,7 +624,7 @@ void add_multi(Candidates<sa::DevModel> &c, const sched_model_t *model, const Mu
   const int B = model->max_batch, n = a.n, total = a.instances * a.chains;
   const int cus = cu_count();
   if (model->policy == SCHED_STATIC &&
-      (sa::reg_form(B) != sa::kRegAny || reg_any_pays((n + a.instances - 1) / a.instances, B))) {
+      (sa::reg_form(B) != sa::kRegAny || sa::reg_any_pays((n + a.instances - 1) / a.instances, B))) {
     const int waves = std::min(sa::reg_shape(total, cus), a.chains);
     const int groups = (a.chains + waves - 1) / waves, grid = a.instances * groups;
     for (int parts = 0; parts <= (sa::reg_form(B) == sa::kRegAny ? 0 : 1); ++parts) {

@@ -211,13 +211,14 @@ def test_uneven_workgroups_fitted(sl, orc, chains):
         assert np.array_equal(rec[c], orc.anneal_chain_fit(q, fo, c, iters, 0.7, 0.99, 5, start_info=info)["rec"]), c
 
 
-# (requests, batch, candidates before the full replay): limit rows and the delta kernel; one batch of
-# up to 32 that holds every request leaves the limit rows out
-@pytest.mark.parametrize("n,B,before", [(2, 17, 1), (30, 32, 1), (32, 32, 1), (65, 32, 2), (66, 64, 2), (50, 64, 2)])
-def test_one_batch_takes_no_limit_rows(sl, orc, n, B, before):
+# (requests, batch, candidates before the full replay): limit rows and the delta kernel; one or two
+# batches of up to 32 leave the limit rows out
+@pytest.mark.parametrize("n,B,before", [(2, 17, 1), (30, 32, 1), (32, 32, 1), (34, 17, 1), (50, 28, 1), (64, 32, 1),
+                                        (65, 32, 2), (66, 64, 2), (50, 64, 2)])
+def test_two_batches_take_no_limit_rows(sl, orc, n, B, before):
     rng = np.random.default_rng(n + B)
     q = random_queue(rng, n, max_in=100, max_out=20, thr_hi=40_000 * n)
-    dq, chains = sl.DeviceQueue.from_queue(q), 2000
+    dq, chains = sl.DeviceQueue.from_queue(q), 2600
     assert _selected(sl, sl.sched_anneal(dq, Model(B, 0, **WIDE), chains, 1, 0.7, 0.99, 3)) == before
     m = Model(B, 0, **COEF)
     ws = sl.sched_anneal(dq, m, chains, 60, 0.7, 0.99, 3)

@@ -83,6 +83,8 @@ def test_delta_kernel_sizes_where_the_spread_is_three(shapes, n, B, chains):
 
 EVAL_SHIM = r"""
 #include "launch_shape.h"
+extern "C" int any_pays(int n, int B, int chains, int cus) { return sa::reg_any_pays(n, B, chains, cus); }
+extern "C" int rows_pay(int n, int B) { return sa::rows_pay(n, B); }
 extern "C" int reg(int chains, int cus) { return sa::reg_shape(chains, cus); }
 extern "C" int grid(long rows, int waves, long lds, int per_simd, double beyond, int lim, int cus) {
   return sa::eval_grid(rows, waves, (size_t)lds, sa::EvalShape{per_simd, beyond}, lim, cus);
@@ -100,7 +102,7 @@ def eval_grid(tmp_path_factory):
     lib.grid.argtypes = [C.c_long, C.c_int, C.c_long, C.c_int, C.c_double, C.c_int, C.c_int]
     def call(rows, waves, lds, per_simd, beyond):
         return lib.grid(rows, waves, lds, per_simd, beyond, LIM, CUS)
-    call.reg = lib.reg
+    call.reg, call.any_pays, call.rows_pay = lib.reg, lib.any_pays, lib.rows_pay
     return call
 
 
@@ -171,3 +173,18 @@ def test_register_kernels_put_one_chain_on_a_simd(eval_grid):
         assert w == 1 if chains <= 2 * CUS else w in (3, 4), chains
         assert chains <= 2 * CUS or w * CUS >= min(chains, 4 * CUS), chains
         assert chains < 4 * CUS or w == 4, chains
+
+
+def test_kernel_of_two_batches(eval_grid):
+    """Two batches of 17 to 32: the register kernel, but the delta kernel between 8 and 16 chains per CU,
+    and never limit rows; one batch: the delta kernel; three and more keep theirs at any chain count."""
+    for B in range(17, 33):
+        for chains in (1, 64, 2048, 2049, 3000, 4096, 4097, 20000):
+            for n in range(2, 65):
+                want = n > B and (n > 2 * B or not 8 * CUS < chains <= 16 * CUS)
+                assert eval_grid.any_pays(n, B, chains, CUS) == want, (n, B, chains)
+        assert [n for n in range(2, 1025) if eval_grid.rows_pay(n, B)] == list(range(2 * B + 1, 32 * B + 1))[:1024 - 2 * B]
+    for B in (3, 5, 12, 15):
+        assert all(eval_grid.any_pays(n, B, 3000, CUS) for n in range(B + 1, 65)) and not eval_grid.rows_pay(400, B)
+    assert all(eval_grid.rows_pay(n, B) for n in (2, 50, 64, 1024) for B in (33, 48, 64))
+    assert not eval_grid.any_pays(64, 33, 1, CUS)
