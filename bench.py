@@ -133,11 +133,11 @@ HEADLINE_KERNEL_SOURCES = ("anneal_wave_rows.h", "anneal_wave.h", "anneal_sized.
                            "device_cont.h", "device_plan.h", "device_replay.h", "device_rng.h", "device_common.h",
                            "launch_shape.h", "lane_shape.h", "sloanneal.hip")
 PROFILE_BY_SOURCE = {
-    # anneal_rows_kernel<0, 16> on the burst workload: 17,420,480 B of HBM traffic (FETCH_SIZE
+    # anneal_rows_kernel<0, 16> on the burst workload: 17,422,016 B of HBM traffic (FETCH_SIZE
     # x 2.0 + WRITE_SIZE x 1.0); 441.7 VALU and 54.9 LDS instructions, 116.3 bank-conflict
     # cycles per proposal
-    "71e5e1e41ac0bed9ba0ebf478bd26fb695a6feaeb32998ea3ac29c5f7e0e17d9": {
-        "traffic": 17420480, "valu_busy": 0.667, "lds_bank_conflict_cycles_per_lds_instr": 2.12,
+    "ef7acd587b24f2f48b91c854e2db16698e6f06d61a48a7ec0559159c4bf04a39": {
+        "traffic": 17422016, "valu_busy": 0.666, "lds_bank_conflict_cycles_per_lds_instr": 2.12,
         "lds_instr_per_chain_iter": 54.9, "vgprs": 89, "lds_bytes_per_workgroup": 129296, "waves_per_simd": 4},
 }
 
